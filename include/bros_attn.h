@@ -182,13 +182,15 @@ int bros_attn_decode(void* out, const void* q,
  *                  16-byte aligned; owned by the caller, contents undefined
  *                  after the call.
  * bf16 runs the QK^T and PV products on the matrix cores (P is rounded to bf16
- * before PV) for max_ctx <= 32768. There the workspace is optional (NULL, or
- * one smaller than the query, is accepted): with it, when the call's (row
- * tile, KV head) units are fewer than the compute units, long units are split
- * over key ranges whose partial results are merged, so idle compute units
- * take a share; without it every unit runs whole. The merged rows differ from
- * the unsplit ones by rounding only. fp32, and bf16 beyond that context, run
- * a vector-ALU path that requires the workspace (BROS_E_WORKSPACE otherwise).
+ * before PV). For max_ctx <= 32768 the workspace is optional (NULL, or one
+ * smaller than the query, is accepted): with it, when the call's (row tile, KV
+ * head) units are fewer than the compute units, long units are split over key
+ * ranges whose partial results are merged, so idle compute units take a share;
+ * without it every unit runs whole. Beyond that context the workspace is
+ * required (BROS_E_WORKSPACE otherwise) and units are split as far as it holds
+ * partials (more than the query's size allows more pieces, up to the size
+ * queried for max_ctx <= 32768). The merged rows differ from the unsplit ones
+ * by rounding only. fp32 runs a vector-ALU path that requires the workspace.
  */
 int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
                             int32_t num_q_tokens, int32_t max_q_len,
@@ -242,9 +244,9 @@ int bros_attn_mixed(void* out_prefill, const void* q_prefill, const int32_t* cu_
  * Bytes of device workspace the call `kind` needs for `num_rows` query rows
  * (num_seqs for decode, num_q_tokens for prefill). Pure host arithmetic; it
  * does not know num_kv_heads and sizes bf16 decode for groups of up to 8
- * query heads. For the bf16 prefill on the matrix cores (max_ctx <= 32768)
- * it returns the size of the optional split workspace, the same for every
- * call. Returns 0 for unsupported arguments.
+ * query heads. For the bf16 prefill with max_ctx <= 32768 it returns the size
+ * of the optional split workspace, the same for every call. Returns 0 for
+ * unsupported arguments.
  */
 size_t bros_attn_workspace_size(int32_t kind, int32_t dtype, int32_t num_rows,
                                 int32_t num_q_heads, int32_t head_dim, int32_t max_ctx);

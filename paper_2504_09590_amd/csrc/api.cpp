@@ -93,7 +93,7 @@ size_t bros_attn_workspace_size(int32_t kind, int32_t dtype, int32_t num_rows,
   const bool bf16 = dtype == BROS_BF16;
   if (kind == BROS_WS_DECODE) return bros::decode_workspace_bytes(num_rows, num_q_heads, max_ctx, bf16);
   if (kind == BROS_WS_PREFILL)
-    return (bf16 && max_ctx <= bros::kPrefillMaxCtxMfma) ? bros::prefill_workspace_bytes()
+    return (bf16 && max_ctx <= bros::kPrefillWholeTableCtx) ? bros::prefill_workspace_bytes()
                                                           : bros::decode_workspace_bytes(num_rows, num_q_heads, max_ctx, bf16);
   return 0;
 }
@@ -174,7 +174,17 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const float scale_log2 = resolve_scale(scale, head_dim);
 
-  if (dtype == BROS_BF16 && max_ctx <= bros::kPrefillMaxCtxMfma) {
+  if (dtype == BROS_BF16) {
+    // Beyond kPrefillWholeTableCtx the workspace is required, at the size the
+    // query gives there, and splits as far as it holds partials.
+    const bool whole_table = max_ctx <= bros::kPrefillWholeTableCtx;
+    if (!whole_table) {
+      if ((long long)num_q_tokens * num_kv_heads * ((max_ctx + 15) / 16) > 0x7fffffffLL)
+        return fail(BROS_E_SHAPE, "%s: more than 2^31 (row, KV head, block) tiles", fn);
+      const size_t need = bros::decode_workspace_bytes(num_q_tokens, num_q_heads, max_ctx, true);
+      if (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 16))
+        return fail(BROS_E_WORKSPACE, "%s: workspace of %zu bytes (16-byte aligned) required, got %zu at %p", fn, need, workspace_bytes, workspace);
+    }
     bros::PrefillArgs a{};
     a.out = out;
     a.q = q;
@@ -198,17 +208,13 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
     a.scale_log2 = scale_log2;
     const long long total = (long long)num_seqs * num_kv_heads * a.tiles_per_seq;
     if (total > 0x7fffffffLL - 1024) return fail(BROS_E_SHAPE, "%s: grid of %lld workgroups too large", fn, total);
-    // the workspace is optional here: with one of the queried size, long units are split
-    if (aligned(workspace, 16)) bros::set_prefill_workspace(a, workspace, workspace_bytes);
+    // up to kPrefillWholeTableCtx the workspace is optional: with one of the queried size, long units are split
+    if (aligned(workspace, 16)) bros::set_prefill_workspace(a, workspace, workspace_bytes, whole_table);
     return launch_status(fn, bros::launch_prefill_mfma(a, group, (int)total, s));
   }
 
-  // fp32 (and bf16 beyond the matrix-core path's context limit): every prefill
-  // row is a decode row with its own causal context.
-  const bool bf16 = dtype == BROS_BF16;
-  if (bf16 && (long long)num_q_tokens * num_kv_heads * ((max_ctx + 15) / 16) > 0x7fffffffLL)
-    return fail(BROS_E_SHAPE, "%s: more than 2^31 (row, KV head, block) tiles", fn);
-  const size_t need = bros::decode_workspace_bytes(num_q_tokens, num_q_heads, max_ctx, bf16);
+  // fp32: every prefill row is a decode row with its own causal context.
+  const size_t need = bros::decode_workspace_bytes(num_q_tokens, num_q_heads, max_ctx, false);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 16)))
     return fail(BROS_E_WORKSPACE, "%s: workspace of %zu bytes (16-byte aligned) required, got %zu at %p", fn, need, workspace_bytes, workspace);
   const bros::DecodePlan plan = bros::plan_decode(num_q_tokens, max_ctx);
@@ -233,8 +239,8 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
   a.split_blocks = plan.split_blocks;
   a.n_split_max = plan.n_split_max;
   a.scale_log2 = scale_log2;
-  bros::set_decode_workspace(a, need > 0 ? workspace : nullptr, bf16);
-  return launch_status(fn, bros::launch_decode(a, group, bf16, s));
+  bros::set_decode_workspace(a, need > 0 ? workspace : nullptr, false);
+  return launch_status(fn, bros::launch_decode(a, group, false, s));
 }
 
 int bros_attn_mixed(void* out_prefill, const void* q_prefill, const int32_t* cu_q, int32_t num_q_tokens,
@@ -253,9 +259,9 @@ int bros_attn_mixed(void* out_prefill, const void* q_prefill, const int32_t* cu_
   if (num_prefill_seqs < 0 || num_decode_seqs < 0 || num_q_tokens < 0 || max_q_len < 0 || max_ctx_prefill < 0 ||
       max_ctx_decode < 0)
     return fail(BROS_E_SHAPE, "%s: negative count", fn);
-  if (max_ctx_prefill > bros::kPrefillMaxCtxMfma)
-    return fail(BROS_E_UNSUPPORTED, "%s: prefill context %d beyond the matrix-core path's %d (use the two calls)", fn,
-                max_ctx_prefill, bros::kPrefillMaxCtxMfma);
+  if (max_ctx_prefill > bros::kPrefillWholeTableCtx)
+    return fail(BROS_E_UNSUPPORTED, "%s: prefill context %d beyond %d (use the two calls)", fn,
+                max_ctx_prefill, bros::kPrefillWholeTableCtx);
   if (!ctx_lens || !block_tables) return fail(BROS_E_NULL, "%s: ctx_lens or block_tables is NULL", fn);
   const int P = num_prefill_seqs, D = num_decode_seqs;
   const size_t tab_off = (size_t)P * max_blocks_per_seq;

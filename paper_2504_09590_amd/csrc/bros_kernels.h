@@ -125,9 +125,9 @@ hipError_t launch_kv_move(const KvMoveArgs& a, bool gather, hipStream_t stream);
 hipError_t launch_decode(DecodeArgs a, int group, bool bf16, hipStream_t stream);
 // Events the bf16 decode records around its decode kernel (both null: none).
 void set_decode_kernel_events(hipEvent_t before, hipEvent_t after);
-// Longest context the matrix-core prefill handles (its block table is staged
-// whole in LDS); longer contexts take the vector path.
-constexpr int32_t kPrefillMaxCtxMfma = 32768;
+// Longest context whose block table the matrix-core prefill stages whole in
+// LDS; longer ones run its ring variant.
+constexpr int32_t kPrefillWholeTableCtx = 32768;
 // Compute units enabled for `stream` (a stream made with
 // hipExtStreamCreateWithCUMask runs on a subset of the device): the device's
 // count is queried once per device, the stream's CU mask read on every call.
@@ -161,7 +161,9 @@ struct MixedModel {
 hipError_t launch_mixed(PrefillArgs pa, DecodeArgs da, MixedModel mm, int group, int num_units, hipStream_t stream);
 int prefill_positions_per_tile(int group);
 // Workspace of the matrix-core prefill (optional: without it no unit is split).
+// With `whole`, only one of at least prefill_workspace_bytes() is used; else
+// any, for as many partials as it holds.
 size_t prefill_workspace_bytes();
-void set_prefill_workspace(PrefillArgs& a, void* ws, size_t bytes);
+void set_prefill_workspace(PrefillArgs& a, void* ws, size_t bytes, bool whole);
 
 }  // namespace bros

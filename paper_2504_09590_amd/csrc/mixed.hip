@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreadsMixed, 2) void mixed_kernel(PrefillArgs pa,
   constexpr int QT = pf::kRows / G;
 
   // ---- 1. this workgroup's prefill unit (none past the last rank)
-  pf::prefill_unit<G, kOff32>(pa, pf::paired_id(pa, blockIdx.x, grid), s_kring, s_vring, &s_first_bad, s_tbl, s_dir);
+  pf::prefill_unit<G, kOff32, false>(pa, pf::paired_id(pa, blockIdx.x, grid), s_kring, s_vring, &s_first_bad, s_tbl, s_dir);
   __syncthreads();   // the rings are free again
 
   // ---- 2. the decode's tile prefix over rows, in the K ring

@@ -3,13 +3,15 @@
 // prefill_device.h.
 #include "prefill_device.h"
 
+#include <algorithm>
+
 namespace bros {
 namespace pf {
 
-template <int G, bool kOff32>
+template <int G, bool kOff32, bool kRing>
 __global__ __launch_bounds__(kThreads, 2) void prefill_mfma_kernel(PrefillArgs a) {
   BROS_PREFILL_UNIT_LDS
-  prefill_unit<G, kOff32>(a, paired_id(a, blockIdx.x, gridDim.x), s_kring, s_vring, &s_first_bad, s_tbl, s_dir);
+  prefill_unit<G, kOff32, kRing>(a, paired_id(a, blockIdx.x, gridDim.x), s_kring, s_vring, &s_first_bad, s_tbl, s_dir);
 }
 
 // Fold the pieces of split units: one workgroup per (split item, KV head),
@@ -77,6 +79,11 @@ __global__ __launch_bounds__(kThreads) void prefill_merge_kernel(PrefillArgs a) 
 // 2 x this many (split piece, KV head) partials.
 constexpr int kMaxPrefillCus = 512;
 
+// The longest context of a call does not fit the LDS copy of a whole table.
+bool prefill_needs_ring(int32_t max_ctx, int32_t max_blocks_per_seq) {
+  return max_ctx > kPrefillWholeTableCtx && max_blocks_per_seq > kMaxTableLds;
+}
+
 template <int G>
 hipError_t launch_group(PrefillArgs a, int num_units, hipStream_t stream) {
   // Split only when the units leave compute units idle: with a unit or more
@@ -86,7 +93,8 @@ hipError_t launch_group(PrefillArgs a, int num_units, hipStream_t stream) {
   if (a.ws_o != nullptr && num_units / a.num_kv_heads <= kMaxRankItems) {
     int cus = stream_compute_units(stream);
     cus = cus < kMaxPrefillCus ? cus : kMaxPrefillCus;
-    if (num_units < cus) a.num_cus = cus;
+    // (a unit cut in two or more leaves at most num_cus + num_units partials)
+    if (num_units < cus && num_units < a.ws_slots - num_units) a.num_cus = std::min(cus, a.ws_slots - num_units);
   }
   // Placement of the first round (two workgroups per compute unit): known
   // when the stream has the whole chip, so unsplit units are paired by work.
@@ -98,10 +106,19 @@ hipError_t launch_group(PrefillArgs a, int num_units, hipStream_t stream) {
   // ranks beyond the units: at most num_cus / Hkv more pieces than items
   const long long grid = (long long)num_units + a.num_cus;
   // (block, KV head) rows of 4 KiB: 32-bit offsets reach them all below 2^20 rows
-  if ((int64_t)a.num_blocks * a.num_kv_heads <= (int64_t)1 << 20)
-    hipLaunchKernelGGL((prefill_mfma_kernel<G, true>), dim3((unsigned)grid), dim3(kThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL((prefill_mfma_kernel<G, false>), dim3((unsigned)grid), dim3(kThreads), 0, stream, a);
+  const bool off32 = (int64_t)a.num_blocks * a.num_kv_heads <= (int64_t)1 << 20;
+  const dim3 g((unsigned)grid), b(kThreads);
+  if (prefill_needs_ring(a.max_ctx, a.max_blocks_per_seq)) {
+    if (off32)
+      hipLaunchKernelGGL((prefill_mfma_kernel<G, true, true>), g, b, 0, stream, a);
+    else
+      hipLaunchKernelGGL((prefill_mfma_kernel<G, false, true>), g, b, 0, stream, a);
+  } else {
+    if (off32)
+      hipLaunchKernelGGL((prefill_mfma_kernel<G, true, false>), g, b, 0, stream, a);
+    else
+      hipLaunchKernelGGL((prefill_mfma_kernel<G, false, false>), g, b, 0, stream, a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.num_cus == 0) return e;
   // split items x Hkv <= num_cus
@@ -118,24 +135,27 @@ using pf::launch_group;
 
 int prefill_positions_per_tile(int group) { return kRows / group; }
 
+constexpr size_t kSlotBytes = (size_t)kRows * (kHeadDim + 2) * sizeof(float);   // one partial: rows, their max and sum
+constexpr size_t kListBytes = (1 + 3 * (size_t)kMaxRankItems) * sizeof(int32_t);
+constexpr int kMaxSlots = 2 * kMaxPrefillCus;
+
 size_t prefill_workspace_bytes() {
-  const size_t rows = 2 * (size_t)kMaxPrefillCus * kRows;   // (split piece, KV head) partials x rows
-  const size_t bytes = rows * kHeadDim * sizeof(float) + rows * 2 * sizeof(float) + (1 + 3 * (size_t)kMaxRankItems) * sizeof(int32_t);
-  return (bytes + 255) & ~(size_t)255;
+  return (kMaxSlots * kSlotBytes + kListBytes + 255) & ~(size_t)255;
 }
 
-void set_prefill_workspace(PrefillArgs& a, void* ws, size_t bytes) {
+void set_prefill_workspace(PrefillArgs& a, void* ws, size_t bytes, bool whole) {
   a.num_cus = 0;
   a.ws_slots = 0;
   a.ws_o = nullptr;
   a.ws_ml = nullptr;
   a.ws_list = nullptr;
-  if (ws == nullptr || bytes < prefill_workspace_bytes()) return;   // no splitting
-  const size_t rows = 2 * (size_t)kMaxPrefillCus * kRows;
+  if (ws == nullptr || bytes < (whole ? prefill_workspace_bytes() : kListBytes)) return;   // no splitting
+  const size_t slots = (bytes - kListBytes) / kSlotBytes;
+  a.ws_slots = slots < kMaxSlots ? (int32_t)slots : kMaxSlots;
+  const size_t rows = (size_t)a.ws_slots * kRows;
   a.ws_o = static_cast<float*>(ws);
   a.ws_ml = a.ws_o + rows * kHeadDim;
   a.ws_list = reinterpret_cast<int32_t*>(a.ws_ml + rows * 2);
-  a.ws_slots = 2 * kMaxPrefillCus;
 }
 
 hipError_t launch_prefill_mfma(PrefillArgs a, int group, int num_tiles_total, hipStream_t stream) {

@@ -40,7 +40,11 @@
 // (block, KV head) row indices, so a load's address is the row times 4 KiB
 // plus the lane's offset (one vector add; below 2^20 rows the pool's rows all
 // lie within 32-bit offsets of its base), and a tile's K and V loads, one
-// step apart, share one index.
+// step apart, share one index. Contexts whose table is longer than that LDS
+// copy (more than kPrefillWholeTableCtx positions) take a variant that keeps
+// a ring of the piece's entries there and refills half of it every 512 tiles
+// (512 rows on 40000 cached tokens, 32 / 8 heads: 415 us, 815 TFLOP/s; as
+// decode rows, each reading its whole context, they took 12.0 ms).
 //
 // The instruction stream of a step is what bounds it (a lone wave issues an
 // instruction every 9 cycles or so), so the step carries as few as it can:
@@ -92,7 +96,8 @@ constexpr int kRowBytes = kHeadDim * 2;            // bytes of one K or V row
 constexpr int kTileBytes = kKeys * kRowBytes;      // one K or V tile in LDS
 constexpr float kRescaleSlack = 8.0f;              // log2 units
 constexpr float kNoMax = -1.0e30f;
-constexpr int kMaxTableLds = kPrefillMaxCtxMfma / kBlockSize;   // table entries staged in LDS
+constexpr int kMaxTableLds = kPrefillWholeTableCtx / kBlockSize;   // table entries staged in LDS
+constexpr int kRefillTiles = kMaxTableLds / 4;     // ring variant: tiles (2 entries each) of half the ring
 constexpr int kTablePad = 32;                      // staged entries past the last tile (loads run ahead)
 constexpr int kMaxRankItems = kThreads;            // units planned on the device (one per thread)
 constexpr int kMaxPieces = 2 * kThreads;           // pieces ranked on the device (two per thread)
@@ -390,8 +395,11 @@ __device__ __forceinline__ int paired_id(const PrefillArgs& a, int b, int grid) 
 
 // One unit (or piece) of the matrix-core prefill: unit id `id` (rank id /
 // Hkv, KV head id % Hkv), run by the calling workgroup's four waves. Every
-// early return is uniform over the workgroup.
-template <int G, bool kOff32>
+// early return is uniform over the workgroup. kRing: the table entries in LDS
+// are a ring over the piece (any context length) instead of the whole table
+// (contexts up to kPrefillWholeTableCtx); the step loop then carries one more
+// scalar test per four tiles, which is why short contexts keep their own variant.
+template <int G, bool kOff32, bool kRing>
 __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8_t* s_kring, uint8_t* s_vring,
                                              int* s_first_bad_p, int* s_tbl, int8_t* s_dir) {
   constexpr int QT = kRows / G;   // positions per unit
@@ -481,8 +489,10 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
   };
   const int my_bt = rg >> 1;                // block of the tile holding this wave's rows
   const int my_slot0 = 8 * (rg & 1);        // first of its slots
+  // Where the LDS copy holds entry b.
+  auto at = [&](int b) -> int { return kRing ? (b & (kMaxTableLds - 1)) : b; };
   // This wave's row index for step j (a vector register holding a uniform value).
-  auto own = [&](int j) -> int { return s_tbl[2 * (kb + j) + my_bt]; };
+  auto own = [&](int j) -> int { return s_tbl[at(2 * (kb + j) + my_bt)]; };
 
   // Loads: load i (0, 1) covers tile rows 8 rg + 4i + lane / 16, lane writing
   // physical chunk lane % 16, which holds logical chunk (lane % 16) ^ swz(row).
@@ -512,7 +522,7 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
   auto fixup_v = [&](int j, uint8_t* ring) __attribute__((always_inline)) {
     if (j >= n_kt) return;
     const int b = 2 * (kb + j) + my_bt;
-    const int dirv = __builtin_amdgcn_readfirstlane((int)s_dir[b]);
+    const int dirv = __builtin_amdgcn_readfirstlane((int)s_dir[at(b)]);
     if (dirv != 0 && (b + 1) * kBlockSize <= ctx) return;
     uint8_t* dv = ring + 8 * rg * kRowBytes;
 #pragma unroll
@@ -584,8 +594,8 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
     if constexpr (decltype(maskc)::value) {
       // visible: valid block, position < ctx and <= the row's position
       const int lim = min(qpos, ctx - 1);
-      const int dir0 = s_dir[2 * tile];       // 0: invalid, past the context or outside the piece
-      const int dir1 = s_dir[2 * tile + 1];
+      const int dir0 = s_dir[at(2 * tile)];   // 0: invalid, past the context or outside the piece
+      const int dir1 = s_dir[at(2 * tile + 1)];
       const bool ok0 = dir0 != 0, ok1 = dir1 != 0;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
@@ -705,19 +715,32 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
   // ahead) are staged as row 0 with direction 0.
   if (tid == 0) (*s_first_bad_p) = bhi;
   __syncthreads();
-  for (int b = blo + tid; b < 2 * (kb + n_kt) + kTablePad; b += kThreads) {
-    int idx = 0, d = 0;
-    if (b < bhi) {
-      const int v = tbl[b];
-      if (v >= 0 && v < a.num_blocks) {
-        idx = v * Hkv + g;
-        d = entry_direction(a.dir, a.cls, a.dir_per_entry, a.max_blocks_per_seq, s, b);
-      } else {
-        atomicMin(s_first_bad_p, b);
-      }
+  // Entry b (table value v), in LDS.
+  auto stage = [&](int b, int v) __attribute__((always_inline)) {
+    const bool good = b < bhi && v >= 0 && v < a.num_blocks;
+    s_tbl[at(b)] = good ? v * Hkv + g : 0;
+    s_dir[at(b)] = good ? (int8_t)entry_direction(a.dir, a.cls, a.dir_per_entry, a.max_blocks_per_seq, s, b) : (int8_t)0;
+  };
+  auto entry_value = [&](int b) -> int { return b < bhi ? tbl[b] : -1; };
+  if constexpr (kRing) {
+    // The ring's first filling; and the whole piece's entries looked over for
+    // the first invalid one, eight loads in flight per thread.
+    for (int b = blo + tid; b < blo + kMaxTableLds; b += kThreads) stage(b, entry_value(b));
+    constexpr int U = 8;
+    for (int b = blo + tid; b < bhi; b += U * kThreads) {
+      int v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = b + u * kThreads < bhi ? tbl[b + u * kThreads] : 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (v[u] < 0 || v[u] >= a.num_blocks) atomicMin(s_first_bad_p, b + u * kThreads);
     }
-    s_tbl[b] = idx;
-    s_dir[b] = (int8_t)d;
+  } else {
+    for (int b = blo + tid; b < 2 * (kb + n_kt) + kTablePad; b += kThreads) {
+      const int v = entry_value(b);
+      if (b < bhi && (v < 0 || v >= a.num_blocks)) atomicMin(s_first_bad_p, b);
+      stage(b, v);
+    }
   }
   __syncthreads();
   const int first_bad = __builtin_amdgcn_readfirstlane((*s_first_bad_p));
@@ -752,11 +775,25 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
   // the V load.
   int ii = 0;
   int iv = w3;
+  // Ring variant, before step ii (a multiple of kRefillTiles): the entries of
+  // the kRefillTiles tiles before it give way to those kRefillTiles ahead of
+  // it. Every wave is past the barrier that ended step ii - 1, so nobody
+  // reads the former any more (step ii reads entries of tiles ii .. ii + 5),
+  // and many barriers lie before the first read of the latter.
+  auto refill = [&]() __attribute__((always_inline)) {
+    if constexpr (kRing) {
+      if (ii != 0 && (ii & (kRefillTiles - 1)) == 0) {
+        const int b0 = 2 * (kb + ii + kRefillTiles);
+        for (int i = tid; i < 2 * kRefillTiles; i += kThreads) stage(b0 + i, entry_value(b0 + i));
+      }
+    }
+  };
   // the piece's tiles below plain_tiles, as a step bound
   const int n_plain = max(0, min(n_kt, plain_tiles - kb));
   auto main_step = [&](auto uc) __attribute__((always_inline)) -> bool {
     constexpr int u = decltype(uc)::value;
     if (ii + 1 >= n_plain) return false;
+    if constexpr (u == 0) refill();   // (u and ii agree mod 4)
     const int ik = own(ii + 5);
     // step ii reads buffer ii % 2 and fills the other (u and ii agree mod 4)
     if constexpr (u % 2 == 0)
@@ -776,6 +813,7 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
   for (; ii + 1 < n_kt; ++ii) {
     const int sl = ii & (kSlots - 1);
     const int sl1 = (sl + 1) & (kSlots - 1);
+    refill();
     const int ik = own(ii + 5);
     step(kr + sl1 * kSlotBytes, vr + sl * kSlotBytes, kb + ii + 1, std::true_type{}, std::true_type{}, sa, sb);
     sa = sb;

@@ -83,9 +83,9 @@ struct PrefillArgs {
   int32_t tiles_per_seq;  // ceil(max_q_len / positions per tile)
   float scale_log2;
   // Splitting long units into pieces over key ranges (none when num_cus is 0):
-  // the compute units the work is spread over, the partials of split units,
-  // [ws_slots][128 rows] x (ws_o: 128 dims, ws_ml: max and sum) in fp32, and
-  // the list of split units that the merge walks (count, then (item, parts,
+  // the compute units the work is spread over, the partials of split units in
+  // fp32, [ws_slots] x (ws_o: the unit's 128 x 128 accumulators as its four
+  // waves hold them, ws_ml: [128 rows] max and sum), and the list of split units that the merge walks (count, then (item, parts,
   // first slot) triples).
   int32_t num_cus;
   int32_t xcd_cus;        // compute units per XCD when the launch has the whole chip, else 0

@@ -19,15 +19,16 @@
 //
 // Balance. All units of a step usually run in one round, so the kernel lasts
 // as long as its longest unit. When the units are fewer than the compute
-// units (a long context under few chunk rows) and a workspace is given, a
-// unit whose key tiles exceed the part size T is split into ceil(tiles / T)
-// pieces over disjoint key ranges, T = ceil(all tiles x Hkv / compute units)
-// (at least kMinPartTiles). A split unit's pieces write unnormalised partial
-// rows with their max and sum; prefill_merge_kernel folds them (the same
-// max-rescaled sum as the decode's merge). Unsplit units write their rows
-// directly. Units (or pieces) are launched longest first, ranked on the device
-// from the length table, and consecutive ids are spread over the XCDs so that
-// one KV head of every sequence stays on one XCD's L2.
+// units (a long context under few chunk rows) and a workspace is given, units
+// longer than a part size T are split into ceil(tiles / T) pieces over
+// disjoint key ranges, T chosen so that all pieces are resident at once
+// (PartSize). A split unit's pieces write unnormalised partial rows with their
+// max and sum; prefill_merge_kernel folds them (the same max-rescaled sum as
+// the decode's merge). Unsplit units write their rows directly. Units (or
+// pieces) are launched longest first, ranked on the device from the length
+// table -- by every wave on its own for up to 64 items, a few hundred
+// instructions without LDS or barriers -- and consecutive ids are spread over
+// the XCDs so that one KV head of every sequence stays on one XCD's L2.
 //
 // Data path. K and V rows go straight from the pool into LDS
 // (global_load_lds, no registers), row-major [key][d] with the 16-byte chunks
@@ -100,8 +101,10 @@ constexpr int kMaxTableLds = kPrefillWholeTableCtx / kBlockSize;   // table entr
 constexpr int kRefillTiles = kMaxTableLds / 4;     // ring variant: tiles (2 entries each) of half the ring
 constexpr int kTablePad = 32;                      // staged entries past the last tile (loads run ahead)
 constexpr int kMaxRankItems = kThreads;            // units planned on the device (one per thread)
-constexpr int kMaxPieces = 2 * kThreads;           // pieces ranked on the device (two per thread)
+constexpr int kMaxPieces = 4 * kThreads;           // pieces ranked on the device (four per thread)
 constexpr int kMinPartTiles = 8;                   // the shortest piece a unit is split into
+constexpr int kMinSavedTiles = 12;                 // what splitting must take off the longest unit
+constexpr int kPairTiles = 96;                     // the shortest pieces that run two to a compute unit
 constexpr int kLoadsPerStep = 4;                   // two K and two V loads per wave per step
 constexpr int kXcds = 8;                           // accelerator dies of the chip; blockIdx % 8 picks the die
 
@@ -258,17 +261,136 @@ struct PiecePlan {
   int q_begin, n, ctx;   // the item's sequence: cu_q[s], cu_q[s + 1] - cu_q[s], ctx_lens[s] (n = -1: not read)
 };
 
+// The part size of a call that splits its long units: T tiles, so that unit i
+// becomes ceil(L_i / T) pieces. All pieces of a round should be resident at
+// once -- one piece too many waits for a whole piece -- so T is the shortest of
+// some candidates between the mean T0 = total / budget and 2 T0 whose pieces
+// fit the budget of pieces per KV head, units shorter than T counting by their
+// length (several share a slot in turn). The budget is one piece per compute
+// unit, and two where pieces of at least kPairTiles tiles remain: two resident
+// workgroups advance 1.2 us per tile each against 0.55 us for one, so two pay
+// only where a tenth of a long piece outweighs the second start-up and the
+// partials (512 rows on 16000 cached tokens: 154 us with two, 163 with one; on
+// 4000: 61 and 59).
+struct PartSize {
+  int budget, t0;
+  __device__ PartSize(const PrefillArgs& a, int total) {
+    budget = max(1, min(2 * a.num_cus, a.ws_slots) / a.num_kv_heads);
+    if (total < kPairTiles * budget) budget = max(1, min(a.num_cus, a.ws_slots) / a.num_kv_heads);
+    t0 = max((total + budget - 1) / budget, kMinPartTiles);
+  }
+  // candidate c of n (c < n): t0 .. 2 t0
+  __device__ int candidate(int c, int n) const { return t0 + (int)((int64_t)t0 * c / (n - 1)); }
+  __device__ float rcp(int c, int n) const { return 1.0f / (float)candidate(c, n); }
+  // What a unit of L tiles takes of the budget at part size 1 / rcp. (A float
+  // quotient one piece off only moves the choice of T.)
+  static __device__ float share(int L, float rcp) {
+    const float x = (float)max(L, 0) * rcp;
+    return x <= 1.0f ? x : ceilf(x - 1e-4f);
+  }
+};
+
+// Whether splitting at part size T pays, the longest unit having Lmax tiles: it
+// must end kMinSavedTiles tiles earlier than whole, or the partials and the
+// merge cost what is saved.
+__device__ __forceinline__ bool split_pays(int Lmax, int T) { return Lmax - T >= kMinSavedTiles; }
+
+__device__ __forceinline__ int wave_inclusive_scan(int v, int lane) {
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int u = __shfl_up(v, o);
+    if (lane >= o) v += u;
+  }
+  return v;
+}
+
+// plan_pieces (below) for at most 64 items: every wave computes the plan by
+// itself, lane i holding item i, without LDS or a barrier.
+template <int QT>
+__device__ PiecePlan plan_pieces_wave(const PrefillArgs& a, int rank) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int tps = a.tiles_per_seq;
+  const int n_items = a.num_seqs * tps;
+  int L = 0, q0 = 0, n = 0, cx = 0;
+  if (lane < n_items) {
+    const int sq = lane / tps;
+    q0 = a.cu_q[sq];
+    n = a.cu_q[sq + 1] - q0;
+    cx = a.ctx_lens[sq];
+    L = unit_tiles_of(a, q0, n, cx, lane - sq * tps, QT);
+  }
+  auto plan_of = [&](int k, int part, int parts, int slot) -> PiecePlan {
+    return PiecePlan{k, part, parts, slot, read_lane_i32(q0, k), read_lane_i32(n, k), read_lane_i32(cx, k)};
+  };
+  // Keys distinct and > 0 for items with tiles; the order of the ranks.
+  auto key_of = [&](int len) -> int { return len > 0 ? len * kWave + (kWave - 1 - lane) : 0; };
+  if (a.num_cus > 0) {
+    const int total = read_lane_i32(wave_inclusive_scan(L, lane), kWave - 1);
+    const PartSize ps(a, total);
+    const float rcp = ps.rcp(lane, kWave);
+    float pieces = 0.0f;
+    int Lmax = 0;
+    for (int i = 0; i < n_items; ++i) {
+      const int Li = read_lane_i32(L, i);
+      pieces += PartSize::share(Li, rcp);
+      Lmax = max(Lmax, Li);
+    }
+    const uint64_t fits = __builtin_amdgcn_ballot_w64(pieces <= (float)ps.budget);
+    const int T = ps.candidate(fits ? __builtin_ctzll(fits) : kWave - 1, kWave);
+    const int P = L > 0 ? 1 + (L - 1) / T : 0;
+    const int own = P > 1 ? P : 0;
+    const int send = wave_inclusive_scan(own, lane);
+    const int n_split = read_lane_i32(send, kWave - 1);
+    const bool split = n_split > 0 && split_pays(Lmax, T) && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+      // the split items, in item order: count, then (item, parts, first slot)
+      const uint64_t m = __builtin_amdgcn_ballot_w64(split && P > 1);
+      const int idx = __builtin_popcountll(m & ((1ull << lane) - 1));
+      if (split && P > 1) {
+        a.ws_list[1 + 3 * idx] = lane;
+        a.ws_list[2 + 3 * idx] = P;
+        a.ws_list[3 + 3 * idx] = send - own;
+      }
+      if (lane == 0) a.ws_list[0] = __builtin_popcountll(m);
+    }
+    if (split) {
+      // items by the length of their pieces; first rank of each item's pieces
+      const int key = key_of(P > 0 ? (L + P - 1) / P : 0);
+      int start = 0;
+      for (int i = 0; i < n_items; ++i) {
+        const int ki = read_lane_i32(key, i), Pi = read_lane_i32(P, i);
+        start += ki > key ? Pi : 0;
+      }
+      const uint64_t m = __builtin_amdgcn_ballot_w64(P > 0 && rank >= start && rank < start + P);
+      if (m == 0) return PiecePlan{-1, 0, 1, 0, 0, -1, 0};
+      const int k = __builtin_ctzll(m);
+      return plan_of(k, rank - read_lane_i32(start, k), read_lane_i32(P, k), read_lane_i32(send - own, k));
+    }
+  }
+  // The item of rank `rank`: the largest key that exactly `rank` keys exceed, by its bits.
+  const int key = key_of(L);
+  int all = key;
+#pragma unroll
+  for (int o = kWave / 2; o >= 1; o >>= 1) all |= __shfl_xor(all, o);
+  all = __builtin_amdgcn_readfirstlane(all);
+  int found = 0;
+  for (int bit = all ? 31 - __builtin_clz(all) : -1; bit >= 0; --bit) {
+    const int cand = found | (1 << bit);
+    if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(key >= cand)) > rank) found = cand;
+  }
+  if (found == 0) return PiecePlan{-1, 0, 1, 0, 0, -1, 0};
+  return plan_of(kWave - 1 - (found & (kWave - 1)), 0, 1, 0);
+}
+
 // The piece of rank `rank` (longest first). Items are (sequence, tile of
 // positions); all KV heads of an item have its length L (key tiles of its
 // last row). Without splitting (num_cus 0) each item is one piece. With it,
-// the part size is T = max(kMinPartTiles, ceil(sum L x Hkv / num_cus)), the
-// mean work of a compute unit, and an item becomes ceil(L / T) pieces; then
-// ranks exceed the items by at most num_cus / Hkv and split pieces times Hkv
-// number at most 2 num_cus. Workgroup 0 writes the list of split items for
-// the merge. `scratch` is 2 kMaxPieces + 4 + kThreads / kWave + 3
-// kMaxRankItems ints of LDS, 16-byte aligned, that nothing else uses
-// meanwhile. Every thread of the workgroup calls it. The lengths read for the
-// ranking come back with the plan, so the unit does not read them again.
+// an item becomes ceil(L / T) pieces (PartSize), and ranks exceed the items by at most 2 num_cus /
+// Hkv. Workgroup 0 writes the list of split items for the merge. `scratch` is
+// 2 kMaxPieces + 4 + kThreads / kWave + 3 kMaxRankItems ints of LDS, 16-byte
+// aligned, that nothing else uses meanwhile. Every thread of the workgroup
+// calls it. The lengths read for the ranking come back with the plan, so the
+// unit does not read them again.
 template <int QT>
 __device__ PiecePlan plan_pieces(const PrefillArgs& a, int rank, int* scratch) {
   const int tid = threadIdx.x;
@@ -279,6 +401,7 @@ __device__ PiecePlan plan_pieces(const PrefillArgs& a, int rank, int* scratch) {
     const int t_rank = rank / a.num_seqs;
     return PiecePlan{t_rank < tps ? (rank % a.num_seqs) * tps + (tps - 1 - t_rank) : -1, 0, 1, 0, 0, -1, 0};
   }
+  if (n_items <= kWave) return plan_pieces_wave<QT>(a, rank);
   int* s_len = scratch;                     // [kMaxPieces] lengths, then -1 padding
   int* s_pid = scratch + kMaxPieces;        // [kMaxPieces] item * 1024 + part
   int* s_res = scratch + 2 * kMaxPieces;    // [4]
@@ -306,13 +429,26 @@ __device__ PiecePlan plan_pieces(const PrefillArgs& a, int rank, int* scratch) {
   if (a.num_cus > 0) {
     int total = 0;
     block_scan(max(L, 0), s_red, &total);
-    const int T = max(kMinPartTiles, (int)(((int64_t)total * a.num_kv_heads + a.num_cus - 1) / a.num_cus));
+    if (tid < n_items) s_len[tid] = L;
+    if (tid == 0) s_res[0] = kThreads - 1;
+    __syncthreads();
+    const PartSize ps(a, total);
+    float pieces = 0.0f;
+    const float rcp = ps.rcp(tid, kThreads);
+    int Lmax = 0;
+    for (int i = 0; i < n_items; ++i) {
+      pieces += PartSize::share(s_len[i], rcp);
+      Lmax = max(Lmax, s_len[i]);
+    }
+    if (pieces <= (float)ps.budget) atomicMin(&s_res[0], tid);
+    __syncthreads();
+    const int T = ps.candidate(s_res[0], kThreads);
     const int Pt = L > 0 ? 1 + (L - 1) / T : 0;
     const int pend = block_scan(Pt, s_red, &n_pieces);
     const int own = Pt > 1 ? Pt : 0;
     int n_split = 0;
     const int send = block_scan(own, s_red, &n_split);
-    split = n_split > 0 && n_pieces <= kMaxPieces && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
+    split = n_split > 0 && split_pays(Lmax, T) && n_pieces <= kMaxPieces && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
     if (split) {
       P = Pt;
       pbase = pend - Pt;
@@ -835,15 +971,14 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
   if (parts > 1) {
     // ---- A piece of a split unit: unnormalised rows plus their max and sum.
     const size_t slot = ((size_t)(pslot + part) * Hkv + g) * kRows + r_unit;
-    float* po = a.ws_o + slot * kHeadDim;
+    // (the accumulators as they lie: every store of the wave is 1 KiB
+    // contiguous, and the merge reads the same order)
+    float4* po = reinterpret_cast<float4*>(a.ws_o + (slot - r_unit + 32 * rg) * kHeadDim) + lane;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
 #pragma unroll
-      for (int jq = 0; jq < 4; ++jq) {
-        const int d0 = 32 * dt + 8 * jq + 4 * half;   // accumulators 4jq..4jq+3 are dims d0..d0+3
-        *reinterpret_cast<float4*>(po + d0) =
-            make_float4(o[dt][4 * jq], o[dt][4 * jq + 1], o[dt][4 * jq + 2], o[dt][4 * jq + 3]);
-      }
+      for (int jq = 0; jq < 4; ++jq)
+        po[(4 * dt + jq) * kWave] = make_float4(o[dt][4 * jq], o[dt][4 * jq + 1], o[dt][4 * jq + 2], o[dt][4 * jq + 3]);
     }
     if (half == 0) {
       a.ws_ml[2 * slot] = m_run;

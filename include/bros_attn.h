@@ -190,7 +190,8 @@ int bros_attn_decode(void* out, const void* q,
  * required (BROS_E_WORKSPACE otherwise) and units are split as far as it holds
  * partials (more than the query's size allows more pieces, up to the size
  * queried for max_ctx <= 32768). The merged rows differ from the unsplit ones
- * by rounding only. fp32 runs a vector-ALU path that requires the workspace.
+ * by rounding only. fp32 runs on the fp32 matrix instructions and requires the
+ * workspace whenever the query's size is not 0.
  */
 int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
                             int32_t num_q_tokens, int32_t max_q_len,

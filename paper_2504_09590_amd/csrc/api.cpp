@@ -213,7 +213,6 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
     return launch_status(fn, bros::launch_prefill_mfma(a, group, (int)total, s));
   }
 
-  // fp32: every prefill row is a decode row with its own causal context.
   const size_t need = bros::decode_workspace_bytes(num_q_tokens, num_q_heads, max_ctx, false);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned(workspace, 16)))
     return fail(BROS_E_WORKSPACE, "%s: workspace of %zu bytes (16-byte aligned) required, got %zu at %p", fn, need, workspace_bytes, workspace);
@@ -230,6 +229,7 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
   a.ctx_lens = ctx_lens;
   a.cu_q = cu_q;
   a.num_rows = num_q_tokens;
+  a.max_q_len = max_q_len;
   a.num_seqs = num_seqs;
   a.num_blocks = num_blocks;
   a.max_blocks_per_seq = max_blocks_per_seq;
@@ -240,7 +240,7 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
   a.n_split_max = plan.n_split_max;
   a.scale_log2 = scale_log2;
   bros::set_decode_workspace(a, need > 0 ? workspace : nullptr, false);
-  return launch_status(fn, bros::launch_decode(a, group, false, s));
+  return launch_status(fn, bros::launch_prefill_f32(a, group, s));
 }
 
 int bros_attn_mixed(void* out_prefill, const void* q_prefill, const int32_t* cu_q, int32_t num_q_tokens,

@@ -25,10 +25,10 @@ struct KvWriteArgs {
   int32_t num_kv_heads;
 };
 
-// Split-K decode over "query rows". In decode mode (cu_q == nullptr) row r is
-// sequence r with context ctx_lens[r]. In row mode (cu_q != nullptr) row r is a
-// prefill row of the sequence s with cu_q[s] <= r < cu_q[s+1] and sees the
-// first ctx_lens[s] - (cu_q[s+1] - r) + 1 positions (causal, diagonal inclusive).
+// Decode rows (cu_q == nullptr): row r is sequence r with context ctx_lens[r].
+// In fp32 also prefill chunks (cu_q != nullptr): row r belongs to the sequence s
+// with cu_q[s] <= r < cu_q[s+1] and sees the first ctx_lens[s] - (cu_q[s+1] -
+// r) + 1 positions (causal, diagonal inclusive).
 struct DecodeArgs {
   void* out;
   const void* q;
@@ -40,7 +40,7 @@ struct DecodeArgs {
   const int32_t* ctx_lens;
   const int32_t* cu_q;
   int32_t dir_per_entry;  // dir is [S][max_blocks_per_seq] (else [S])
-  // Partial results. fp32 split-K: [rows][Hq][n_split_max] slots. bf16 (one
+  // Partial results. fp32: [rows][Hq][n_split_max] slots. bf16 (one
   // worker per wave over an even share of the tiles): slot (row * Hkv + g +
   // worker) * G + head-in-group, for segments cut between workers.
   float* ws_acc;          // [slots][D] unnormalised partial outputs
@@ -57,8 +57,10 @@ struct DecodeArgs {
   int32_t max_ctx;
   int32_t num_q_heads;
   int32_t num_kv_heads;
-  int32_t split_blocks;   // blocks per split, multiple of 4, <= 64
-  int32_t n_split_max;
+  int32_t split_blocks;   // fp32: blocks per split (multiple of 4, <= 64; the prefill may take several of them at once)
+  int32_t n_split_max;    // fp32: splits the workspace is laid out for
+  int32_t max_q_len;      // fp32 chunks: host bound of a sequence's rows
+  int32_t tiles_per_seq;  // fp32 chunks: units of a sequence per KV head (set by the launch)
   float scale_log2;       // softmax scale * log2(e)
 };
 
@@ -123,6 +125,7 @@ void set_decode_workspace(DecodeArgs& a, void* ws, bool bf16);
 hipError_t launch_kv_write(const KvWriteArgs& a, bool bf16, hipStream_t stream);
 hipError_t launch_kv_move(const KvMoveArgs& a, bool gather, hipStream_t stream);
 hipError_t launch_decode(DecodeArgs a, int group, bool bf16, hipStream_t stream);
+hipError_t launch_prefill_f32(const DecodeArgs& a, int group, hipStream_t stream);
 // Events the bf16 decode records around its decode kernel (both null: none).
 void set_decode_kernel_events(hipEvent_t before, hipEvent_t after);
 // Longest context whose block table the matrix-core prefill stages whole in

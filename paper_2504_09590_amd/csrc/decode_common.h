@@ -1,5 +1,5 @@
-// Pieces shared by the two decode paths: bf16 on the matrix cores
-// (decode.hip) and fp32 on the vector ALU (decode_f32.hip).
+// Pieces shared by the bf16 decode (decode.hip) and the fp32 decode and
+// prefill (decode_f32.hip, prefill_f32.hip).
 #pragma once
 
 #include "bros_device.h"
@@ -33,31 +33,15 @@ __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {   // round 
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, b2_t));
 }
 
-// Query row -> (sequence, visible context). Decode mode: row r is sequence r.
-// Row mode: row r is a prefill row and sees its causal prefix.
+// Decode row r is sequence r and sees its whole context.
 __device__ __forceinline__ void resolve_row(const DecodeArgs& a, int row, int& s, int& ctx) {
-  if (a.cu_q == nullptr) {
-    s = row;
-    ctx = a.ctx_lens[s];
-  } else {
-    s = min(upper_index(a.cu_q, a.num_seqs + 1, row), a.num_seqs - 1);
-    ctx = a.ctx_lens[s] - (a.cu_q[s + 1] - row) + 1;
-  }
-  ctx = min(ctx, a.max_ctx);
+  s = row;
+  ctx = min(a.ctx_lens[s], a.max_ctx);
   ctx = min(ctx, a.max_blocks_per_seq * kBlockSize);
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
 hipError_t launch_decode_f32(const DecodeArgs& a, int group, hipStream_t stream);
+// Folds the split partials of every row whose context took more than one split of a.split_blocks blocks.
+hipError_t launch_f32_merge(const DecodeArgs& a, hipStream_t stream);
 
 }  // namespace bros

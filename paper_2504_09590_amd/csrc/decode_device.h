@@ -1,8 +1,7 @@
 // Device code of the bf16 decode on the matrix cores, shared by the decode
 // launch (decode.hip) and the fused prefill|decode launch (mixed.hip).
 // bros_attn_decode (bf16) on gfx950: paged decode attention over the
-// bidirectional pool on the matrix cores (fp32 runs on the vector ALU,
-// decode_f32.hip).
+// bidirectional pool on the matrix cores (fp32: decode_f32.hip).
 //
 // What it computes (Sec. 2.1 decode attention over the cached KV; Sec. 5.1
 // bidirectional slot order; Sec. 6 direction-aware paged kernel): for query

@@ -496,12 +496,18 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
 
 // Combine the split partials of every (row, head) whose context needed more
 // than one split: o = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i.
-__global__ __launch_bounds__(kHeadDim) void decode_f32_merge_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(kHeadDim) void f32_merge_kernel(DecodeArgs a) {
   const int hq = blockIdx.x % a.num_q_heads;
   const int row = blockIdx.x / a.num_q_heads;
   const int d = threadIdx.x;
   int s, ctx;
-  resolve_row(a, row, s, ctx);
+  if (a.cu_q == nullptr) {
+    resolve_row(a, row, s, ctx);
+  } else {   // a chunk's row and the positions it sees
+    s = min(upper_index(a.cu_q, a.num_seqs + 1, row), a.num_seqs - 1);
+    ctx = a.ctx_lens[s] - (a.cu_q[s + 1] - row) + 1;
+    ctx = min(ctx, min(a.max_ctx, a.max_blocks_per_seq * kBlockSize));
+  }
   if (ctx <= 0) return;
   const int nblk = (ctx + kBlockSize - 1) / kBlockSize;
   const int nsp = (nblk + a.split_blocks - 1) / a.split_blocks;
@@ -527,12 +533,15 @@ hipError_t launch_group_f32(const DecodeArgs& a, hipStream_t stream, int slot) {
   hipLaunchKernelGGL((decode_f32_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_split_max <= 1) return e;
-  hipLaunchKernelGGL(decode_f32_merge_kernel, dim3((unsigned)(a.num_rows * a.num_q_heads)), dim3(kHeadDim), 0,
-                     stream, a);
-  return hipGetLastError();
+  return launch_f32_merge(a, stream);
 }
 
 }  // namespace
+
+hipError_t launch_f32_merge(const DecodeArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL(f32_merge_kernel, dim3((unsigned)(a.num_rows * a.num_q_heads)), dim3(kHeadDim), 0, stream, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_decode_f32(const DecodeArgs& a, int group, hipStream_t stream) {
   switch (group) {

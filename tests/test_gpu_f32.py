@@ -1,0 +1,69 @@
+"""fp32 chunks on the matrix instructions, and fp32 decode rows: the edges of the
+16-slot blocks, of the four waves that share a unit, of splits over workgroups
+and of units of 16 / G positions, all group sizes, both directions, and
+non-finite V rows that only later rows see. Against the oracle at the fp32 bar
+of every other kernel test (1e-5)."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2504_09590_amd import workload as W
+from tests.gpu_helpers import announce, compare, poison_unowned, require_gpu, with_direction_table
+from tests.test_gpu_decode import ref_decode, run_decode
+from tests.test_gpu_prefill import chunk_batch, ref_prefill, run_prefill, written
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("group,hkv", [(1, 8), (2, 3), (4, 2), (8, 1)])
+def test_chunks_all_groups_ragged(group, hkv):
+    require_gpu()
+    b = written(chunk_batch([0, 1, 15, 16, 700, 0], [1, 17, 33, 100, 65, 0], [W.RT, W.BE] * 3, group=group, hkv=hkv,
+                            dtype="f32", seed=40 + group))
+    poison_unowned(b)
+    b = with_direction_table(b, seed=group)
+    announce(f"f32 chunks G={group} Hkv={hkv}")
+    compare(run_prefill(b), ref_prefill(b), "f32", f"f32 chunks G={group}")
+
+
+@pytest.mark.parametrize("c0,n", [(4000, 1), (4090, 7), (1023, 2), (511, 16), (16 * 64 - 5, 9)])
+def test_few_rows_on_a_long_context_split(c0, n):
+    # few units: their blocks go to several workgroups, and rows of one unit may need different numbers of splits
+    require_gpu()
+    b = written(chunk_batch([c0], [n], [W.RT], group=2, hkv=2, dtype="f32", seed=n))
+    poison_unowned(b)
+    announce(f"f32 chunk c0={c0} n={n}, split")
+    compare(run_prefill(b), ref_prefill(b), "f32", f"f32 c0={c0} n={n}")
+
+
+@pytest.mark.parametrize("group", [1, 4, 8])
+@pytest.mark.parametrize("rows", [1, 5, 300])
+def test_decode_rows_split_and_whole(group, rows):
+    require_gpu()
+    rng = np.random.default_rng(rows)
+    ctx = [int(x) for x in rng.integers(1, 5000 if rows < 10 else 200, rows)]
+    ctx[0] = 5000 if rows < 10 else 128       # the longest fills whole blocks
+    b = W.custom(ctx, [i % 2 for i in range(rows)], 2 * group, 2, dtype="f32", seed=rows + group, spare_blocks=3)
+    if rows == 300:
+        b.ctx_lens[7] = 0                     # a row without context is zeros
+    poison_unowned(b)
+    announce(f"f32 decode rows={rows} G={group}")
+    compare(run_decode(b), ref_decode(b), "f32", f"f32 decode rows={rows} G={group}")
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_non_finite_values_of_later_positions(value):
+    # position 37 holds a non-finite V row: rows before it must not notice, whatever shares their unit
+    require_gpu()
+    b = written(chunk_batch([20], [40], [W.RT], group=2, hkv=2, dtype="f32", seed=9))
+    blk, slot = oracle.physical_location(b.block_tables, b.dir, 0, np.array([37]))
+    ref = ref_prefill(b)
+    b.v_pool[blk[0], :, slot[0], 5] = value
+    announce(f"f32 chunk with a V row of {value}")
+    got = run_prefill(b)
+    before = 37 - 20
+    compare(got[:before], ref[:before], "f32", "rows before the non-finite position")
+    assert not np.isfinite(got[before:, :, 5]).any()
+    rest = [d for d in range(128) if d != 5]
+    compare(got[before:][:, :, rest], ref[before:][:, :, rest], "f32", "other dims")

@@ -18,23 +18,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int nch = (a.num_rows + chunk - 1) / chunk;
   const int total = build_tile_prefix(a, s_pre, s_scan, chunk, nch);
 
-  // Each wave takes an equal share of the tiles; with fewer tiles than waves
-  // the last waves idle, so every worker has at least one tile. Workgroup 0
-  // records the partition for the merge.
-  const int workers = min(a.num_workers, total);
+  // Workgroup 0 records the shares for the merge. While there are fewer
+  // workers than waves, they spread over the workgroups.
+  const Shares shares(a, total);
+  const int workers = shares.workers;
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) a.ws_wstart[0] = workers;
-    for (int w = threadIdx.x; w <= workers; w += kThreads)
-      a.ws_wstart[1 + w] = (int)((int64_t)w * total / max(workers, 1));
+    for (int w = threadIdx.x; w <= workers; w += kThreads) a.ws_wstart[1 + w] = shares.start(w);
   }
-  const int wid = blockIdx.x * kWaves + wave_id_uniform();
+  const int wave = wave_id_uniform();
+  const int wid = workers < a.num_workers ? wave * gridDim.x + blockIdx.x : blockIdx.x * kWaves + wave;
   if (wid >= workers) {
-    if (wid < a.num_workers && (threadIdx.x & (kWave - 1)) == 0) a.ws_cut[2 * wid] = -1;   // idle: nothing to merge
+    if ((threadIdx.x & (kWave - 1)) == 0) a.ws_cut[2 * wid] = -1;   // idle: nothing to merge
     return;
   }
-  const int t0 = (int)((int64_t)wid * total / workers);
-  const int t1 = (int)((int64_t)(wid + 1) * total / workers);
-  decode_worker<G>(a, s_pre, chunk, nch, wid, t0, t1 - t0, total, workers);
+  // (Kept in vector registers: with the share in scalar ones the compiler packs
+  // the kernel into 149 registers with scalar spills and its waves get slower,
+  // 169 us against 166 on 64 rows, 37 against 30 on one row of 8000 tokens.)
+  int t0 = shares.start(wid), t1 = shares.start(wid + 1);
+  asm volatile("" : "+v"(t0), "+v"(t1));
+  decode_worker<G>(a, s_pre, chunk, nch, wid, t0, t1 - t0, &shares);
 }
 
 // Segments cut between workers: o = sum_w 2^(m_w - M) acc_w / sum_w 2^(m_w -
@@ -48,18 +51,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 // were written as zeros by that worker (a worker that sees no tile of a row
 // never runs for it: rows without context have no tiles, so they are written
 // here). The G heads of the segment share the wave: 64 / G lanes per head,
-// each folding 2 G of its head's dims, eight partials in flight. (Merging
+// each folding 2 G of its head's dims, eight partials in flight. A segment of
+// more than kAlone partials (few rows, long contexts) is folded by the four
+// waves of the workgroup together, a fourth of the partials each. (Merging
 // inside the decode kernel instead would need device-scope release/acquire
 // between workgroups, which on this chip writes back and invalidates a whole
-// L2 per segment; the kernel boundary is far cheaper.)
+// L2 per segment; the kernel boundary is far cheaper.) Six rows of 90 to 2048
+// tokens: 14.5 us when a wave folded all of a segment's 30 to 60 partials and
+// every wave took a tile or two, 5.9 us now.
 constexpr int kMergeWaves = 4;
+// Partials that a wave folds by itself, in two rounds. (With one round alone, 8,
+// the longest contexts of 64 rows go to the whole workgroup after its own
+// segments: 6.0 us a merge against 5.4.)
+constexpr int kAlone = 16;
+static_assert(kMergeWaves * kWave == kThreads, "the merge's workgroup");
 
 template <int G>
 __global__ __launch_bounds__(kMergeWaves * kWave) void decode_mfma_merge_kernel(DecodeArgs a) {
   constexpr int L = kWave / G;          // lanes per head
   constexpr int DPL = kHeadDim / L;     // dims per lane (2 G)
+  __shared__ float s_acc[kMergeWaves][DPL][kWave], s_m[kMergeWaves][kWave], s_l[kMergeWaves][kWave];
   const int lane = threadIdx.x & (kWave - 1);
-  const int item = blockIdx.x * kMergeWaves + wave_id_uniform();
+  const int wave = wave_id_uniform();
+  const int item = blockIdx.x * kMergeWaves + wave;
   // Rows without context have no tiles, so no worker saw them: zeros.
   if (item < a.num_rows) {
     int s0, ctx0;
@@ -69,127 +83,157 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void decode_mfma_merge_kernel(
       for (int i = lane; i < a.num_q_heads * kHeadDim / 2; i += kWave) z[i] = 0u;
     }
   }
-  // every worker of the grid wrote its cut-list entry (idle ones -1)
-  if (item >= a.num_workers) return;
-  const int code = a.ws_cut[2 * item];
-  if (code < 0) return;
   const int nkv = a.num_kv_heads;
-  const int row = __builtin_amdgcn_readfirstlane(code / nkv);
-  const int g = __builtin_amdgcn_readfirstlane(code - (code / nkv) * nkv);
-  const int w0 = item;
-  int w1 = __builtin_amdgcn_readfirstlane(a.ws_cut[2 * item + 1]);
   // the decode grid's partition of the tiles: workers W, worker w's tiles
   // start at starts[w] (starts[W] = all tiles); a worker may have none, but
-  // not under the even split (w1 given)
+  // not where the entry names the last worker
   const int32_t* starts = a.ws_wstart + 1;
-  const bool even = w1 >= 0;
-  if (!even) {
+  // The cut-list entries of the workgroup's workers, on every wave (every
+  // worker of the grid wrote its entry, idle ones -1; num_workers is a multiple
+  // of the four): segment and last worker.
+  if (blockIdx.x * kMergeWaves >= a.num_workers) return;
+  int codes[kMergeWaves], lasts[kMergeWaves];
+#pragma unroll
+  for (int e = 0; e < kMergeWaves; ++e) {
+    codes[e] = load_uniform(a.ws_cut, 2 * (blockIdx.x * kMergeWaves + e));
+    lasts[e] = load_uniform(a.ws_cut, 2 * (blockIdx.x * kMergeWaves + e) + 1);
+  }
+  const int2 own = reinterpret_cast<const int2*>(a.ws_cut)[item];
+  const int code = __builtin_amdgcn_readfirstlane(own.x);
+  int w1 = __builtin_amdgcn_readfirstlane(own.y);
+  const bool known = w1 >= 0;
+  if (code >= 0 && !known) {
     // w1: the worker holding the segment's last tile (the last worker whose
     // share starts at or before it), found 64 workers per step
     const int workers = a.ws_wstart[0];
+    const int row = code / nkv, g = code - row * nkv;
     int s, ctx;
     resolve_row(a, row, s, ctx);
     const int nblk = (ctx + kBlockSize - 1) / kBlockSize;
     const int64_t last_tile = (int64_t)a.ws_rows[row] + (int64_t)g * nblk + nblk - 1;
-    w1 = w0;
-    for (int base = w0 + 1; base < workers; base += kWave) {
+    w1 = item;
+    for (int base = item + 1; base < workers; base += kWave) {
       const int w = base + lane;
       const bool before = w < workers && starts[w] <= last_tile;
       const uint64_t m = __builtin_amdgcn_ballot_w64(before);
       w1 = base + __builtin_popcountll(m) - 1;
       if (m != ~0ull) break;
     }
-    w1 = __builtin_amdgcn_readfirstlane(max(w1, w0));
+    w1 = __builtin_amdgcn_readfirstlane(max(w1, item));
   }
-  // a worker with no tiles wrote no partial
-  auto has_tiles = [&](int w) -> bool { return even || starts[w + 1] > starts[w]; };
+
   const int hl = lane / L, sub = lane % L;
-  const size_t seg = (size_t)row * nkv + g;
-  float Lsum = 0.0f, M = kNoMax;
+  float Lsum, M;
   float acc[DPL];
+  // Partials of workers [c0, c1] of segment `seg` folded into (M, Lsum, acc);
+  // M and acc of the head in every lane, Lsum spread over the head's lanes.
+  auto fold = [&](size_t seg, int c0, int c1, bool even) __attribute__((always_inline)) {
+    // a worker with no tiles wrote no partial
+    auto has_tiles = [&](int w) -> bool { return even || starts[w + 1] > starts[w]; };
+    M = kNoMax;
+    Lsum = 0.0f;
 #pragma unroll
-  for (int d = 0; d < DPL; ++d) acc[d] = 0.0f;
-  // Fold partials c + u, u < cnt <= 8, of the head: lane j0 + u of the head's
-  // lanes holds partial c + u's weight in wt and whether its worker had tiles
-  // (and so wrote it) in ok; v[u] holds partial c + u's dims of this lane.
-  // Padding and partials of workers without tiles add zero: their slots may
-  // hold anything.
-  auto fold8 = [&](int cnt, int j0, const float2 (&v)[8][DPL / 2], float wt, int ok) __attribute__((always_inline)) {
+    for (int d = 0; d < DPL; ++d) acc[d] = 0.0f;
+    // up to eight partials a round, their sums requested together with their maxima
+    for (int c = c0; c <= c1; c += 8) {
+      const int cnt = min(8, c1 - c + 1);
+      float2 v[8][DPL / 2];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + min(u, cnt - 1);
-      const float w = __shfl(wt, hl * L + j);
-      const bool use = u < cnt && __shfl(ok, hl * L + j) != 0;
-      const float wu = use ? w : 0.0f;
+      for (int u = 0; u < 8; ++u) {   // indices clamped in range
+        const float2* src = reinterpret_cast<const float2*>(a.ws_acc + ((seg + c + min(u, cnt - 1)) * G + hl) * kHeadDim + sub * DPL);
 #pragma unroll
-      for (int q = 0; q < DPL / 2; ++q) {
-        const float2 x = use ? v[u][q] : make_float2(0.0f, 0.0f);
-        acc[2 * q] = fmaf(x.x, wu, acc[2 * q]);
-        acc[2 * q + 1] = fmaf(x.y, wu, acc[2 * q + 1]);
+        for (int q = 0; q < DPL / 2; ++q) v[u][q] = src[q];
       }
-    }
-  };
-  auto load8 = [&](int c, int cnt, float2 (&v)[8][DPL / 2]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {   // indices clamped in range
-      const int j = min(u, cnt - 1);
-      const float2* src = reinterpret_cast<const float2*>(a.ws_acc + ((seg + c + j) * G + hl) * kHeadDim + sub * DPL);
-#pragma unroll
-      for (int q = 0; q < DPL / 2; ++q) v[u][q] = src[q];
-    }
-  };
-  if (w1 - w0 < 8) {
-    // Up to eight partials (the common case): their sums are requested
-    // together with their maxima, in one round of loads.
-    const int cnt = w1 - w0 + 1;
-    float2 v[8][DPL / 2];
-    load8(w0, cnt, v);
-    const int ok = sub < cnt && has_tiles(w0 + sub);
-    float m_l = kNoMax, l_l = 0.0f;
-    if (ok) {
-      const size_t slot = (seg + w0 + sub) * G + hl;
-      m_l = a.ws_ml[2 * slot];
-      l_l = a.ws_ml[2 * slot + 1];
-    }
-    M = fmaxf(M, m_l);
-#pragma unroll
-    for (int o = L / 2; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    float wt = 0.0f;
-    if (ok) {
-      wt = fast_exp2(m_l - M);
-      Lsum = fmaf(l_l, wt, Lsum);
-    }
-    fold8(cnt, 0, v, wt, ok);
-  } else {
-    // the head's max over the partials (lanes of the head take every L-th one)
-    for (int w = w0 + sub; w <= w1; w += L)
-      if (has_tiles(w)) M = fmaxf(M, a.ws_ml[2 * ((seg + w) * G + hl)]);
-#pragma unroll
-    for (int o = L / 2; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    for (int c = w0; c <= w1; c += L) {
-      // lane sub holds the weight of partial c + sub of its head
-      float wt = 0.0f;
-      const int ok = c + sub <= w1 && has_tiles(c + sub);
+      // lane `sub` of the head holds partial c + sub's maximum and sum
+      const int ok = sub < cnt && has_tiles(c + sub);
+      float m_l = kNoMax, l_l = 0.0f;
       if (ok) {
         const size_t slot = (seg + c + sub) * G + hl;
-        wt = fast_exp2(a.ws_ml[2 * slot] - M);
-        Lsum = fmaf(a.ws_ml[2 * slot + 1], wt, Lsum);
+        m_l = a.ws_ml[2 * slot];
+        l_l = a.ws_ml[2 * slot + 1];
       }
-      const int cnt = min(L, w1 - c + 1);
-      for (int j0 = 0; j0 < cnt; j0 += 8) {
-        float2 v[8][DPL / 2];
-        load8(c + j0, min(8, cnt - j0), v);
-        fold8(min(8, cnt - j0), j0, v, wt, ok);
+      float Mn = fmaxf(M, m_l);
+#pragma unroll
+      for (int o = L / 2; o >= 1; o >>= 1) Mn = fmaxf(Mn, __shfl_xor(Mn, o));
+      if (c > c0) {
+        const float alpha = fast_exp2(M - Mn);
+        Lsum *= alpha;
+#pragma unroll
+        for (int d = 0; d < DPL; ++d) acc[d] *= alpha;
+      }
+      M = Mn;
+      float wt = 0.0f;
+      if (ok) {
+        wt = fast_exp2(m_l - M);
+        Lsum = fmaf(l_l, wt, Lsum);
+      }
+      // Padding and partials of workers without tiles add zero by selection:
+      // their slots may hold anything.
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = min(u, cnt - 1);
+        const float w = __shfl(wt, hl * L + j);
+        const bool use = u < cnt && __shfl(ok, hl * L + j) != 0;
+        const float wu = use ? w : 0.0f;
+#pragma unroll
+        for (int q = 0; q < DPL / 2; ++q) {
+          const float2 x = use ? v[u][q] : make_float2(0.0f, 0.0f);
+          acc[2 * q] = fmaf(x.x, wu, acc[2 * q]);
+          acc[2 * q + 1] = fmaf(x.y, wu, acc[2 * q + 1]);
+        }
       }
     }
+#pragma unroll
+    for (int o = L / 2; o >= 1; o >>= 1) Lsum += __shfl_xor(Lsum, o);
+  };
+  auto write = [&](int seg) __attribute__((always_inline)) {
+    const int row = seg / nkv, g = seg - row * nkv;
+    const float inv = Lsum > 0.0f ? 1.0f / Lsum : 0.0f;
+    uint32_t* out = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) +
+                                                ((size_t)row * a.num_q_heads + g * G + hl) * kHeadDim + sub * DPL);
+#pragma unroll
+    for (int d = 0; d < DPL; d += 2) out[d / 2] = pack2_bf16(acc[d] * inv, acc[d + 1] * inv);
+  };
+
+  // Up to kAlone partials (nearly every segment of a large batch), or a last
+  // worker that had to be found: the wave alone.
+  if (code >= 0 && (w1 - item < kAlone || !known)) {
+    fold((size_t)code, item, w1, known);
+    write(code);
   }
+  // More (long contexts of few rows): the workgroup's waves take a part of them
+  // each and fold their results through LDS.
 #pragma unroll
-  for (int o = L / 2; o >= 1; o >>= 1) Lsum += __shfl_xor(Lsum, o);
-  const float inv = Lsum > 0.0f ? 1.0f / Lsum : 0.0f;
-  uint32_t* out = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) +
-                                              ((size_t)row * a.num_q_heads + g * G + hl) * kHeadDim + sub * DPL);
+  for (int e = 0; e < kMergeWaves; ++e) {
+    const int seg = codes[e], c0 = blockIdx.x * kMergeWaves + e, c1 = lasts[e];
+    if (seg < 0 || c1 - c0 < kAlone) continue;   // uniform over the workgroup
+    const int n = c1 - c0 + 1;
+    const int p0 = c0 + n * wave / kMergeWaves, p1 = c0 + n * (wave + 1) / kMergeWaves - 1;   // (n > kAlone: none is empty)
+    fold((size_t)seg, p0, p1, true);
+    __syncthreads();   // the last segment's results have been read
+    s_m[wave][lane] = M;
+    s_l[wave][lane] = Lsum;
 #pragma unroll
-  for (int d = 0; d < DPL; d += 2) out[d / 2] = pack2_bf16(acc[d] * inv, acc[d + 1] * inv);
+    for (int d = 0; d < DPL; ++d) s_acc[wave][d][lane] = acc[d];
+    __syncthreads();
+    if (wave == e) {
+      float m[kMergeWaves];
+      M = kNoMax;
+#pragma unroll
+      for (int x = 0; x < kMergeWaves; ++x) M = fmaxf(M, m[x] = s_m[x][lane]);
+      Lsum = 0.0f;
+#pragma unroll
+      for (int d = 0; d < DPL; ++d) acc[d] = 0.0f;
+#pragma unroll
+      for (int x = 0; x < kMergeWaves; ++x) {
+        const float wt = fast_exp2(m[x] - M);
+        Lsum = fmaf(s_l[x][lane], wt, Lsum);
+#pragma unroll
+        for (int d = 0; d < DPL; ++d) acc[d] = fmaf(s_acc[x][d][lane], wt, acc[d]);
+      }
+      write(seg);
+    }
+  }
 }
 
 }  // namespace dm

@@ -51,6 +51,8 @@ namespace dm {
 constexpr int kMaxSplitBlocks = 64;   // fp32 split-K: blocks per split at most
 // Tiles whose K/V loads a bf16 decode wave keeps in flight (register sets).
 constexpr int kDepth = 2;
+// Tiles a wave takes at least, where segments are long enough.
+constexpr int kLeastTiles = 4;
 
 // ---------------------------------------------------------------------------
 // bf16 decode on the matrix cores. Per 16-slot block of one (row, KV head), the
@@ -198,15 +200,37 @@ static __device__ void locate(const DecodeArgs& a, const int* s_pre, int chunk, 
 }
 
 
+// The even split of the tiles over the grid's waves, the same on every
+// workgroup. With fewer tiles than waves the last waves idle; and while a wave
+// would get less than kLeastTiles tiles, fewer waves take more, down to one
+// tile where segments are short: a tile costs a wave about 1 us, a segment cut
+// in many pieces costs the merge a round per eight of them. Decode calls, us,
+// with at least 1 / 2 / 4 / 8 tiles a wave: 6 rows of 90 to 2048 tokens (32 / 8
+// heads, 64 blocks a segment) 19.8 / 17.6 / 17.5 / 21.9, one row of 8000 30.0 /
+// 29.4 / 23.6 / 24.0, one of 300 10.1 / 11.0 / 11.7 / 14.7, two of 50 to 100
+// 9.3 / 10.5 / 12.2 / 15.7.
+struct Shares {
+  int workers;   // waves with tiles
+  int total;     // tiles
+
+  __device__ Shares(const DecodeArgs& a, int total_) : total(total_) {
+    const int mean = total / (a.num_rows * a.num_kv_heads);   // blocks of a segment
+    const int least = max(1, min(kLeastTiles, mean / 16));
+    workers = min(a.num_workers, (total + least - 1) / least);
+  }
+  // First tile of worker w (w <= workers).
+  __device__ int start(int w) const { return (int)((int64_t)w * total / max(workers, 1)); }
+  // The worker that holds tile t: the largest w with start(w) <= t.
+  __device__ int holder(int t) const { return (int)((((int64_t)t + 1) * workers - 1) / total); }
+};
+
 // One worker's share: tiles [t0, t0 + n) of the (row, KV head, block) order
 // (n >= 1), the tile prefix over rows in LDS (s_pre, chunk, nch) as
 // build_tile_prefix left it. Run by one wave; `wid` names its partial slots.
-// With `workers` > 0 the shares are the even split of `total` tiles over
-// `workers` workers, so the worker holding any tile is known in closed form;
-// 0 leaves that to the merge.
+// `shares` tells the worker that holds any tile; without it the merge finds it.
 template <int G>
 __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int* s_pre, int chunk, int nch, int wid,
-                                              int t0, int n, int total, int workers) {
+                                              int t0, int n, const Shares* shares) {
   static_assert(G >= 1 && G <= 16, "heads of a group must fit the 16 MFMA columns");
   const int lane = threadIdx.x & (kWave - 1);
   const int grp = lane >> 4;
@@ -316,14 +340,10 @@ __device__ __forceinline__ void decode_worker(const DecodeArgs& a, const int* s_
     if (i + 1 == n) {
       // this worker's entry of the cut list: the segment it started and
       // leaves unfinished (the merge folds it), else -1; and the worker that
-      // holds the segment's last tile, the largest w with
-      // floor(w total / workers) <= that tile (-1: the merge finds it)
+      // holds the segment's last tile (-1: the merge finds it)
       const bool starts_cut = whole && c0.b != c0.nblk - 1;
       int w1 = -1;
-      if (starts_cut && workers > 0) {
-        const int64_t last = (int64_t)t0 + i + (c0.nblk - 1 - c0.b);
-        w1 = (int)(((last + 1) * workers - 1) / total);
-      }
+      if (starts_cut && shares != nullptr) w1 = shares->holder(t0 + i + (c0.nblk - 1 - c0.b));
       if (lane == 0) {
         a.ws_cut[2 * wid] = starts_cut ? c0.row * nkv + c0.g : -1;
         a.ws_cut[2 * wid + 1] = w1;

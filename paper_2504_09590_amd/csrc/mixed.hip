@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kThreadsMixed, 2) void mixed_kernel(PrefillArgs pa,
     if ((tid & (kWave - 1)) == 0) da.ws_cut[2 * wid] = -1;   // no tiles: nothing for the merge
     return;
   }
-  dm::decode_worker<G>(da, s_pre, chunk, nch, wid, t0, t1 - t0, 0, 0);   // (uneven shares: the merge finds the last worker)
+  dm::decode_worker<G>(da, s_pre, chunk, nch, wid, t0, t1 - t0, nullptr);   // (uneven shares: the merge finds the last worker)
 }
 
 template <int G>

@@ -10,9 +10,17 @@
 // step's new tokens, [n][Hkv][D], so a checkpoint is one contiguous buffer
 // that an asynchronous copy moves to or from pinned host memory while the
 // compute units run attention. Pure byte movement in 16-byte chunks; each
-// thread requests all of its chunks before it stores any.
+// thread requests all of its chunks before it stores any. A workgroup moves
+// whole ids of one tensor, as many as one pass of its threads holds (or one id
+// in several passes), so a chunk's place takes 32-bit arithmetic and no
+// division; with 64-bit divisions per chunk the index arithmetic took as long
+// as the bytes: 4096 slots of 8 KV heads (16.8 MB read, 16.8 MB written) 13.0 us a
+// gather and 12.6 a scatter, now 8.8 and 7.6 (3.8 and 4.4 TB/s moved); 64
+// slots 7.4 us, now 4.4 and 3.6.
 #include "bros_device.h"
 #include "bros_kernels.h"
+
+#include <algorithm>
 
 namespace bros {
 namespace {
@@ -22,68 +30,82 @@ constexpr int kIter = 8;   // 16-byte chunks per thread
 
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 
-template <bool GATHER>
-__global__ __launch_bounds__(kThreads) void kv_move_kernel(KvMoveArgs a) {
-  const int tid = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * (kThreads * kIter);
-  const int row_chunks = a.row_bytes / 16;                 // chunks of one (slot, head) row
-  const int64_t per_tensor = (int64_t)a.num_kv_heads * row_chunks;
-  const int64_t per_id = 2 * per_tensor;
-  const int64_t total = (int64_t)a.num_slots * per_id;
-  const int64_t pool_slots = (int64_t)a.num_blocks * kBlockSize;
+// n / d for 0 <= n < 2^24 and d >= 1, with rcp = 1 / d: the float estimate is
+// within one of the quotient, and one correction step makes it exact.
+__device__ __forceinline__ int div_small(int n, int d, float rcp) {
+  int q = (int)((float)n * rcp);
+  const int r = n - q * d;
+  q += (r >= d) ? 1 : 0;
+  q -= (r < 0) ? 1 : 0;
+  return q;
+}
 
-  v4u_t data[kIter];
-  int64_t dst[kIter];   // byte offset of the chunk's destination, -1 when skipped
-  bool to_v[kIter];
+template <bool GATHER, int ROW_CHUNKS>
+__global__ __launch_bounds__(kThreads) void kv_move_kernel(KvMoveArgs a, int ids_per_group, float rcp) {
+  const int tid = threadIdx.x;
+  const int per_id = a.num_kv_heads * ROW_CHUNKS;          // chunks of an id's rows of one tensor
+  const int i0 = blockIdx.x * ids_per_group;
+  const int n = min(ids_per_group, a.num_slots - i0) * per_id;
+  const int64_t pool_slots = (int64_t)a.num_blocks * kBlockSize;
+  const bool v = blockIdx.y != 0;
+  uint8_t* pool = static_cast<uint8_t*>(v ? a.v_pool : a.k_pool);
+  uint8_t* dense = static_cast<uint8_t*>(v ? a.v_dense : a.k_dense) + (size_t)i0 * per_id * 16;
+
+  for (int base = 0; base < n; base += kThreads * kIter) {
+    v4u_t data[kIter];
+    int64_t at[kIter];   // byte offset of the chunk in the pool, -1 when its id lies outside
 #pragma unroll
-  for (int it = 0; it < kIter; ++it) {
-    const int64_t idx = base + (int64_t)it * kThreads + tid;
-    dst[it] = -1;
-    to_v[it] = false;
-    if (idx >= total) continue;
-    const int64_t i = idx / per_id;
-    const int64_t rem = idx - i * per_id;
-    const int tensor = rem >= per_tensor;                  // 0 = K, 1 = V
-    const int64_t c = rem - tensor * per_tensor;           // chunk within the id's rows of that tensor
-    const int64_t h = c / row_chunks;
-    const int64_t cc = c - h * row_chunks;
-    const int64_t sid = a.slot_ids[i];
-    const bool inside = sid >= 0 && sid < pool_slots;
-    const int64_t pool_off = (((sid / kBlockSize) * a.num_kv_heads + h) * kBlockSize + sid % kBlockSize) *
-                                 (int64_t)a.row_bytes + cc * 16;
-    const int64_t dense_off = (i * a.num_kv_heads + h) * (int64_t)a.row_bytes + cc * 16;
-    to_v[it] = tensor != 0;
-    if (GATHER) {
-      const uint8_t* src = static_cast<const uint8_t*>(tensor ? a.v_pool : a.k_pool);
-      data[it] = inside ? *reinterpret_cast<const v4u_t*>(src + pool_off) : v4u_t{0u, 0u, 0u, 0u};
-      dst[it] = dense_off;
-    } else if (inside) {
-      const uint8_t* src = static_cast<const uint8_t*>(tensor ? a.v_dense : a.k_dense);
-      data[it] = *reinterpret_cast<const v4u_t*>(src + dense_off);
-      dst[it] = pool_off;
+    for (int it = 0; it < kIter; ++it) {
+      const int c = min(base + it * kThreads + tid, n - 1);
+      const int i = div_small(c, per_id, rcp);
+      const int rem = c - i * per_id;
+      const int h = rem / ROW_CHUNKS, cc = rem % ROW_CHUNKS;   // (shifts)
+      const int sid = a.slot_ids[i0 + i];
+      at[it] = sid >= 0 && sid < pool_slots
+                   ? ((((int64_t)(sid / kBlockSize) * a.num_kv_heads + h) * kBlockSize + sid % kBlockSize) * ROW_CHUNKS + cc) * 16
+                   : -1;
+      if (!GATHER) data[it] = *reinterpret_cast<const v4u_t*>(dense + (size_t)c * 16);
     }
-  }
+    if (GATHER) {
 #pragma unroll
-  for (int it = 0; it < kIter; ++it) {
-    if (dst[it] < 0) continue;
-    uint8_t* out = GATHER ? static_cast<uint8_t*>(to_v[it] ? a.v_dense : a.k_dense)
-                          : static_cast<uint8_t*>(to_v[it] ? a.v_pool : a.k_pool);
-    *reinterpret_cast<v4u_t*>(out + dst[it]) = data[it];
+      for (int it = 0; it < kIter; ++it) {
+        data[it] = v4u_t{0u, 0u, 0u, 0u};
+        if (at[it] >= 0) data[it] = *reinterpret_cast<const v4u_t*>(pool + at[it]);
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < kIter; ++it) {
+      const int c = base + it * kThreads + tid;
+      if (c >= n) continue;
+      if (GATHER) *reinterpret_cast<v4u_t*>(dense + (size_t)c * 16) = data[it];
+      else if (at[it] >= 0) *reinterpret_cast<v4u_t*>(pool + at[it]) = data[it];
+    }
   }
 }
 
 }  // namespace
 
-hipError_t launch_kv_move(const KvMoveArgs& a, bool gather, hipStream_t stream) {
-  const int64_t total = (int64_t)a.num_slots * 2 * a.num_kv_heads * (a.row_bytes / 16);
-  const int64_t grid = (total + kThreads * kIter - 1) / (kThreads * kIter);
-  if (grid == 0) return hipSuccess;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (gather)
-    hipLaunchKernelGGL(kv_move_kernel<true>, dim3((unsigned)grid), dim3(kThreads), 0, stream, a);
+template <bool GATHER>
+static hipError_t launch_move(const KvMoveArgs& a, hipStream_t stream) {
+  const int row_chunks = a.row_bytes / 16;
+  const int per_id = a.num_kv_heads * row_chunks;
+  const int ids = std::max(1, kThreads * kIter / per_id);   // one pass per workgroup where an id's rows fit one
+  const int64_t groups = ((int64_t)a.num_slots + ids - 1) / ids;
+  if (groups == 0) return hipSuccess;
+  if (groups > 0x7fffffffLL / kThreads) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)groups, 2);
+  const float rcp = 1.0f / (float)per_id;
+  if (row_chunks == kHeadDim * 2 / 16)
+    hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 2 / 16>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
+  else if (row_chunks == kHeadDim * 4 / 16)
+    hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 4 / 16>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
   else
-    hipLaunchKernelGGL(kv_move_kernel<false>, dim3((unsigned)grid), dim3(kThreads), 0, stream, a);
+    return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+hipError_t launch_kv_move(const KvMoveArgs& a, bool gather, hipStream_t stream) {
+  return gather ? launch_move<true>(a, stream) : launch_move<false>(a, stream);
 }
 
 }  // namespace bros

@@ -13,6 +13,10 @@ import os
 from dataclasses import dataclass
 
 import numpy as np
+# torch's HIP runtime first: the library's libamdhip64.so.7 dependency then
+# resolves to that already-mapped copy, so the process runs ONE HIP runtime and
+# device pointers and streams from torch are valid here.
+import torch
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libbros_attn.so")
 
@@ -42,10 +46,6 @@ class BrosError(RuntimeError):
 def _load() -> ctypes.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2504_09590_amd.build`")
-    # Load torch's HIP runtime first: the library's libamdhip64.so.7 dependency
-    # then resolves to that already-mapped copy, so the process runs ONE HIP
-    # runtime and device pointers and streams from torch are valid here.
-    import torch  # noqa: F401
     lib = ctypes.CDLL(LIB_PATH)
     P, I, F, Z = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_size_t
     lib.bros_status_str.argtypes = [ctypes.c_int]
@@ -101,7 +101,7 @@ def _ptr(t) -> int | None:
     """Device (or host numpy) address of a contiguous buffer; None passes NULL."""
     if t is None:
         return None
-    if isinstance(t, np.ndarray):
+    if type(t) is not torch.Tensor and isinstance(t, np.ndarray):
         if not t.flags["C_CONTIGUOUS"]:
             raise ValueError("numpy array must be C-contiguous")
         return t.ctypes.data
@@ -110,8 +110,12 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
+def _rows_from(t, first: int) -> int:
+    """Address of rows [first, ...) of a contiguous tensor (what t[first:] would give, without the view)."""
+    return _ptr(t) + first * t.stride(0) * t.element_size()
+
+
 def _dtype_code(t) -> int:
-    import torch
     if t.dtype == torch.float32:
         return BROS_F32
     if t.dtype == torch.bfloat16:
@@ -120,9 +124,12 @@ def _dtype_code(t) -> int:
 
 
 def _stream(stream) -> int | None:
+    if type(stream) is int:
+        return stream
     if stream is not None:
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
-    import torch
+    if torch.cuda.is_initialized():   # the current stream's handle without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -142,7 +149,7 @@ def _dir_mode(dir, block_tables) -> int:
 
 def bros_kv_write(k_new, v_new, k_pool, v_pool, block_tables, dir, cls, pos0, cu_new, stream=None):
     """Store new tokens' K/V ([Tn][Hkv][D]) in their bidirectional slots of the pools."""
-    nb, hkv, bs, d = (int(x) for x in k_pool.shape)
+    nb, hkv, bs, d = k_pool.shape
     _check(LIB.bros_kv_write(_ptr(k_new), _ptr(v_new), _numel0(k_new), _ptr(k_pool), _ptr(v_pool), nb,
                              _ptr(block_tables), int(block_tables.shape[1]), _ptr(dir), _ptr(cls),
                              _dir_mode(dir, block_tables), _ptr(pos0), _ptr(cu_new), int(cu_new.shape[0]) - 1, hkv, d, bs,
@@ -165,12 +172,25 @@ def bros_attn_workspace_size(kind: int, dtype: int, num_rows: int, num_q_heads: 
 def bros_attn_decode(out, q, k_pool, v_pool, block_tables, dir, cls, ctx_lens, max_ctx: int,
                      scale: float = 0.0, workspace=None, stream=None):
     """out[s][h] = attention of q[s][h] over sequence s's paged context."""
-    nb, hkv, bs, d = (int(x) for x in k_pool.shape)
+    nb, hkv, bs, d = k_pool.shape
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(LIB.bros_attn_decode(_ptr(out), _ptr(q), _ptr(k_pool), _ptr(v_pool), nb, _ptr(block_tables),
                                 int(block_tables.shape[1]), _ptr(dir), _ptr(cls), _dir_mode(dir, block_tables),
                                 _ptr(ctx_lens), int(max_ctx), int(ctx_lens.shape[0]), int(q.shape[1]), hkv, d, bs,
                                 float(scale), _dtype_code(q), _ptr(workspace), ws_bytes, _stream(stream)))
+
+
+def attn_decode_from(first: int, out, q, k_pool, v_pool, block_tables, dir, cls, ctx_lens, max_ctx: int,
+                     workspace=None, stream=None):
+    """bros_attn_decode over the sequences [first, S) of a batch's metadata (out
+    and q hold those rows only), without a view of every array."""
+    nb, hkv, bs, d = k_pool.shape
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    _check(LIB.bros_attn_decode(_ptr(out), _ptr(q), _ptr(k_pool), _ptr(v_pool), nb, _rows_from(block_tables, first),
+                                block_tables.shape[1], _rows_from(dir, first), _rows_from(cls, first),
+                                _dir_mode(dir, block_tables), _rows_from(ctx_lens, first), int(max_ctx),
+                                ctx_lens.shape[0] - first, q.shape[1], hkv, d, bs, 0.0, _dtype_code(q),
+                                _ptr(workspace), ws_bytes, _stream(stream)))
 
 
 def bros_attn_decode_noalloc(out, q, k_pool, v_pool, block_tables, dir, cls, ctx_lens, max_ctx: int,
@@ -188,7 +208,7 @@ def bros_attn_decode_noalloc(out, q, k_pool, v_pool, block_tables, dir, cls, ctx
 def bros_attn_prefill_chunk(out, q, cu_q, max_q_len: int, k_pool, v_pool, block_tables, dir, cls,
                             ctx_lens, max_ctx: int, scale: float = 0.0, workspace=None, stream=None):
     """Causal attention of each prefill chunk's rows over its sequence's paged context."""
-    nb, hkv, bs, d = (int(x) for x in k_pool.shape)
+    nb, hkv, bs, d = k_pool.shape
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(LIB.bros_attn_prefill_chunk(_ptr(out), _ptr(q), _ptr(cu_q), int(q.shape[0]), int(max_q_len),
                                        _ptr(k_pool), _ptr(v_pool), nb, _ptr(block_tables),
@@ -196,6 +216,19 @@ def bros_attn_prefill_chunk(out, q, cu_q, max_q_len: int, k_pool, v_pool, block_
                                        _dir_mode(dir, block_tables), _ptr(ctx_lens), int(max_ctx), int(ctx_lens.shape[0]), int(q.shape[1]), hkv, d, bs,
                                        float(scale), _dtype_code(q), _ptr(workspace), ws_bytes,
                                        _stream(stream)))
+
+
+def attn_prefill_until(num_seqs: int, out, q, cu_q, max_q_len: int, k_pool, v_pool, block_tables, dir, cls,
+                       ctx_lens, max_ctx: int, workspace=None, stream=None):
+    """bros_attn_prefill_chunk over the sequences [0, num_seqs) of a batch's
+    metadata, without a view of every array."""
+    nb, hkv, bs, d = k_pool.shape
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    _check(LIB.bros_attn_prefill_chunk(_ptr(out), _ptr(q), _ptr(cu_q), q.shape[0], int(max_q_len), _ptr(k_pool),
+                                       _ptr(v_pool), nb, _ptr(block_tables), block_tables.shape[1], _ptr(dir),
+                                       _ptr(cls), _dir_mode(dir, block_tables), _ptr(ctx_lens), int(max_ctx),
+                                       num_seqs, q.shape[1], hkv, d, bs, 0.0, _dtype_code(q), _ptr(workspace),
+                                       ws_bytes, _stream(stream)))
 
 
 def bros_attn_mixed(out_prefill, q_prefill, cu_q, max_q_len: int, max_ctx_prefill: int, out_decode, q_decode,
@@ -281,7 +314,6 @@ def bros_check_slot_ids(slot_ids: np.ndarray, num_blocks: int) -> None:
 def bros_stream_create_cu_share(first_cu: int, num_cus: int):
     """A torch stream wrapping a new hipStream_t limited to compute units
     [first_cu, first_cu + num_cus); release it with bros_stream_destroy."""
-    import torch
     handle = ctypes.c_void_p()
     _check(LIB.bros_stream_create_cu_share(int(first_cu), int(num_cus), ctypes.byref(handle)))
     return torch.cuda.ExternalStream(handle.value)
@@ -313,7 +345,6 @@ class DeviceBatch:
 
 
 def _tensor(x: np.ndarray, dtype: str | None, device):
-    import torch
     if dtype == "bf16":
         t = torch.from_numpy(np.ascontiguousarray(x).view(np.int16)).view(torch.bfloat16)
     else:
@@ -336,7 +367,6 @@ def to_device(batch, device="cuda") -> DeviceBatch:
 
 def to_host_bits(t) -> np.ndarray:
     """Device tensor -> numpy (bf16 as uint16 bit patterns, fp32 as float32)."""
-    import torch
     t = t.detach().contiguous().cpu()
     if t.dtype == torch.bfloat16:
         return t.view(torch.int16).numpy().view(np.uint16)

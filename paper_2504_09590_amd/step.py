@@ -145,18 +145,17 @@ class MixedStep:
     def prefill(self, stream=None):
         if self.P == 0:
             return
-        d, P = self.dev, self.P
-        bros.bros_attn_prefill_chunk(self.out_prefill, d.q_prefill, d.cu_q, self.max_q_len, d.k_pool, d.v_pool,
-                                     d.block_tables[:P], d.dir[:P], d.cls[:P], d.ctx_lens[:P],
-                                     self.max_ctx_pre, workspace=self.ws_prefill, stream=stream)
+        d = self.dev
+        bros.attn_prefill_until(self.P, self.out_prefill, d.q_prefill, d.cu_q, self.max_q_len, d.k_pool, d.v_pool,
+                                d.block_tables, d.dir, d.cls, d.ctx_lens, self.max_ctx_pre,
+                                workspace=self.ws_prefill, stream=stream)
 
     def decode(self, stream=None):
         if self.S == self.P:
             return
-        d, P = self.dev, self.P
-        bros.bros_attn_decode(self.out_decode, d.q_decode, d.k_pool, d.v_pool, d.block_tables[P:], d.dir[P:],
-                              d.cls[P:], d.ctx_lens[P:], self.max_ctx_dec, workspace=self.ws_decode,
-                              stream=stream)
+        d = self.dev
+        bros.attn_decode_from(self.P, self.out_decode, d.q_decode, d.k_pool, d.v_pool, d.block_tables, d.dir, d.cls,
+                              d.ctx_lens, self.max_ctx_dec, workspace=self.ws_decode, stream=stream)
 
     def mixed(self, stream=None):
         """Both halves in one launch (bros_attn_mixed)."""
@@ -168,6 +167,17 @@ class MixedStep:
     def run(self, write: bool = True):
         """Enqueue one whole step on the current stream (plus the side stream
         when overlapping); returns (prefill output, decode output)."""
+        if self.main is None and self.swap is None and not self.overlap:
+            # every call on the current stream: its handle, looked up once
+            cur = bros._stream(None)
+            if write:
+                self.kv_write(cur)
+            if self.fused:
+                self.mixed(cur)
+            else:
+                self.prefill(cur)
+                self.decode(cur)
+            return self.out_prefill, self.out_decode
         cur = torch.cuda.current_stream()
         main = self.main if self.main is not None else cur
         if main is not cur:

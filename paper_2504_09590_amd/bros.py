@@ -112,6 +112,8 @@ def _ptr(t) -> int | None:
 
 def _rows_from(t, first: int) -> int:
     """Address of rows [first, ...) of a contiguous tensor (what t[first:] would give, without the view)."""
+    if t is None:
+        raise TypeError("a tensor is needed")
     return _ptr(t) + first * t.stride(0) * t.element_size()
 
 

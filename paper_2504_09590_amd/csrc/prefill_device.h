@@ -47,11 +47,15 @@
 // (512 rows on 40000 cached tokens, 32 / 8 heads: 415 us, 815 TFLOP/s; as
 // decode rows, each reading its whole context, they took 12.0 ms).
 //
-// The instruction stream of a step is what bounds it (a lone wave issues an
-// instruction every 9 cycles or so), so the step carries as few as it can:
-// no 64-bit address arithmetic, the row sums of P as two more matrix-core
-// products (a ones operand times P^T) instead of eight dependent dot
-// products, and the rescale factor computed only when the max moves.
+// What bounds a step: the card's power, with two workgroups per compute unit
+// (the matrix cores are busy 0.63 of the clocks, and the clock falls from 2.4
+// to 1.8 GHz), so the step carries as few instructions as it can: no 64-bit
+// address arithmetic, the rescale factor computed only when the max moves, the
+// row sums of P as eight packed dot products. (Two more matrix products with a
+// ones operand instead of the dot products cost 2-4 % everywhere: four prompts
+// of 4096 rows 538 us against 526, 512 rows on 16000 cached tokens 143 against
+// 139, on 40000 372 against 358, the mixed step's chunks 58.3 against 56.4, all
+// 32 / 8 heads on one card.)
 //
 // Software pipeline (per wave, per step): the scores S^T = K Q^T of the next
 // tile are computed on the matrix cores while the vector ALU turns the current
@@ -689,14 +693,8 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) o[dt] = floatx16{};
   float m_run = kNoMax, m_prev = kNoMax;
-  // Row sums of P on the matrix cores: a ones operand times P^T gives, in
-  // every accumulator of lane l, the sum over the tile's keys of row l % 32
-  // (both half-waves get the whole sum). Only element 0 is read (and
-  // rescaled); the others accumulate along unread.
-  floatx16 lacc = floatx16{};
   const bf16x2_t one2 = {(__bf16)1.0f, (__bf16)1.0f};
-  const v4u_t ones4 = {__builtin_bit_cast(uint32_t, one2), __builtin_bit_cast(uint32_t, one2),
-                       __builtin_bit_cast(uint32_t, one2), __builtin_bit_cast(uint32_t, one2)};
+  float l0 = 0.0f, l1 = 0.0f;   // the row's sum over the keys this half-wave holds, in two chains
   // Raw scores of the wave's next tile, carried from the step that computes
   // them (and their max) to the step that turns them into probabilities: two
   // buffers, so that a step reads one while the matrix cores write the other
@@ -749,8 +747,7 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
     m_run = mx > m_run + kRescaleSlack ? mx : m_run;
   };
   // P = exp2(S * scale - m) rounded to bf16 (the P^T operands); the row sums
-  // (lacc) add exactly these rounded weights, the ones the PV product
-  // applies. Operand c2 (16 keys) holds accumulators 8*c2 .. 8*c2 + 7.
+  // add exactly these rounded weights, the ones the PV product applies. Operand c2 (16 keys) holds accumulators 8*c2 .. 8*c2 + 7.
   auto probs = [&](bf16x8_t (&pf)[2], const floatx16& cur) __attribute__((always_inline)) {
 #pragma unroll
     for (int c2 = 0; c2 < 2; ++c2) {
@@ -760,6 +757,8 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
         const float2_t pp = {fast_exp2(fmaf(cur[8 * c2 + 2 * w], sl2, -m_run)),
                              fast_exp2(fmaf(cur[8 * c2 + 2 * w + 1], sl2, -m_run))};
         pw[w] = __builtin_convertvector(pp, bf16x2_t);   // round to nearest even
+        if (w & 1) l1 = __builtin_amdgcn_fdot2_f32_bf16(pw[w], one2, l1, false);
+        else l0 = __builtin_amdgcn_fdot2_f32_bf16(pw[w], one2, l0, false);
       }
       const v4u_t pk = {__builtin_bit_cast(uint32_t, pw[0]), __builtin_bit_cast(uint32_t, pw[1]),
                         __builtin_bit_cast(uint32_t, pw[2]), __builtin_bit_cast(uint32_t, pw[3])};
@@ -781,7 +780,6 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
       o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vv[dt]), pf[c2], o[dt], 0, 0, 0);
-    lacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ones4), pf[c2], lacc, 0, 0, 0);
   };
   // Rare (lazy max).
   auto rescale_o = [&]() __attribute__((always_inline)) {
@@ -789,7 +787,8 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
       const float alpha = fast_exp2(m_prev - m_run);
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
-      lacc[0] *= alpha;
+      l0 *= alpha;
+      l1 *= alpha;
     }
   };
 
@@ -967,7 +966,7 @@ __device__ __forceinline__ void prefill_unit(const PrefillArgs& a, int id, uint8
     ++ii;
   }
   wait_vmem<0>();
-  const float l_run = lacc[0];
+  const float l_run = pair_sum(l0 + l1);
   if (parts > 1) {
     // ---- A piece of a split unit: unnormalised rows plus their max and sum.
     const size_t slot = ((size_t)(pslot + part) * Hkv + g) * kRows + r_unit;

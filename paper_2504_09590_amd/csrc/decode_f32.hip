@@ -7,7 +7,7 @@
 //     out[r][h] = sum_p softmax_p(scale * q[r][h] . K[p][g]) V[p][g],  p < ctx(r).
 // fp32 products and sums throughout (the fp32 tolerance is 1e-5).
 //
-// Work. An item is (row, KV head, split of up to `split_blocks` blocks). A
+// Work. An item is (row, KV head, split of up to `split_blocks` <= 64 blocks). A
 // persistent grid walks the item list, workgroup w taking items w, w + grid,
 // ...; each workgroup first builds, in LDS, the prefix count of items per
 // row, so an item index maps to its row by binary search.
@@ -35,6 +35,8 @@
 // decode.hip). Rows of a wave, then streams of the workgroup (through LDS),
 // then splits (merge kernel) are combined with max-rescaling.
 #include "decode_common.h"
+
+#include <algorithm>
 
 namespace bros {
 namespace {
@@ -524,15 +526,32 @@ __global__ __launch_bounds__(kHeadDim) void f32_merge_kernel(DecodeArgs a) {
   static_cast<float*>(a.out)[((size_t)row * a.num_q_heads + hq) * kHeadDim + d] = L > 0.0f ? A / L : 0.0f;
 }
 
+constexpr int kItems = 512, kMaxItemBlocks = 32, kWholeBlocks = 20;
+
 template <int G>
-hipError_t launch_group_f32(const DecodeArgs& a, hipStream_t stream, int slot) {
-  const long long padded = (long long)a.num_rows * a.num_kv_heads * a.n_split_max;
+hipError_t launch_group_f32(DecodeArgs a, hipStream_t stream, int slot) {
+  // The plan's split (the workspace is laid out for it) counts rows alone; KV
+  // heads make items too, and a split costs an item's start-up and a partial.
+  // So an item takes as many of the plan's splits as leaves about kItems items,
+  // up to kMaxItemBlocks blocks, and a context of kWholeBlocks or less stays
+  // whole, which saves the merge's launch. Decode calls, us, the plan's splits
+  // and these (32 / 8 heads): 64 rows of 30 to 300 tokens 33 / 23, 16 rows of 64
+  // to 2048 54 / 40, 8 rows of 1000 to 4000 71 / 47, 64 rows of 500 to 2048 141
+  // / 135 (144 with 64 blocks an item), one row 21 both ways.
+  const int maxblk = std::max(1, std::min((a.max_ctx + kBlockSize - 1) / kBlockSize, a.max_blocks_per_seq));
+  const long long segments = (long long)a.num_rows * a.num_kv_heads;
+  const long long want = (kItems + segments - 1) / segments;   // splits of the longest context
+  int per = std::min((int)((maxblk + want - 1) / want), kMaxItemBlocks);
+  if (maxblk <= kWholeBlocks) per = maxblk;
+  a.split_blocks = (per + a.split_blocks - 1) / a.split_blocks * a.split_blocks;
+  const int splits = (maxblk + a.split_blocks - 1) / a.split_blocks;
+  const long long padded = segments * splits;
   const int resident = resident_workgroups(reinterpret_cast<const void*>(&decode_f32_kernel<G>), kThreads, slot, stream);
   const int grid = (int)(padded < resident ? padded : resident);
   if (grid <= 0) return hipSuccess;
   hipLaunchKernelGGL((decode_f32_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.n_split_max <= 1) return e;
+  if (e != hipSuccess || splits <= 1) return e;
   return launch_f32_merge(a, stream);
 }
 

@@ -308,16 +308,22 @@ std::atomic<hipEvent_t> g_kernel_ev_before{nullptr}, g_kernel_ev_after{nullptr};
 
 template <int G>
 hipError_t launch_group(DecodeArgs a, hipStream_t stream, int slot) {
-  int grid = resident_workgroups(reinterpret_cast<const void*>(&dm::decode_mfma_kernel<G>), kThreads, slot, stream);
-  grid = grid < kMaxDecodeGrid ? grid : kMaxDecodeGrid;
-  a.num_workers = grid * kWaves;
   const hipEvent_t before = g_kernel_ev_before.load(), after = g_kernel_ev_after.load();
   hipError_t e = hipSuccess;
   if (before != nullptr && (e = hipEventRecord(before, stream)) != hipSuccess) return e;
-  hipLaunchKernelGGL((dm::decode_mfma_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
-  e = hipGetLastError();
+  const bool whole = decode_is_short(a);
+  if (whole) {
+    e = launch_decode_short(a, G, stream);
+  } else {
+    int grid = resident_workgroups(reinterpret_cast<const void*>(&dm::decode_mfma_kernel<G>), kThreads, slot, stream);
+    grid = grid < kMaxDecodeGrid ? grid : kMaxDecodeGrid;
+    a.num_workers = grid * kWaves;
+    hipLaunchKernelGGL((dm::decode_mfma_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess) return e;
   if (after != nullptr && (e = hipEventRecord(after, stream)) != hipSuccess) return e;
+  if (whole) return hipSuccess;
   return launch_decode_merge(a, G, stream);
 }
 

@@ -98,7 +98,7 @@ __device__ __forceinline__ int row_tiles(const DecodeArgs& a, int row) {
 // in its own entry; a scan within each wave and one across the waves (one
 // barrier) gives every thread its start, and the thread turns its entries
 // into prefixes. `s_scan` holds kThreads / kWave ints.
-static __device__ int build_tile_prefix(const DecodeArgs& a, int* s_pre, int* s_scan, int chunk, int nch) {
+[[maybe_unused]] static __device__ int build_tile_prefix(const DecodeArgs& a, int* s_pre, int* s_scan, int chunk, int nch) {
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), w = tid / kWave;
   const int per = (nch + kThreads - 1) / kThreads;   // chunks per thread
@@ -182,7 +182,7 @@ __device__ __forceinline__ void advance(const DecodeArgs& a, Cursor& c) {
 }
 
 // Tile t (< total): binary search over the chunk prefix, then rows of the chunk.
-static __device__ void locate(const DecodeArgs& a, const int* s_pre, int chunk, int nch, int t, Cursor& c) {
+[[maybe_unused]] static __device__ void locate(const DecodeArgs& a, const int* s_pre, int chunk, int nch, int t, Cursor& c) {
   int ch = upper_index(s_pre, nch + 1, t);
   ch = min(ch, nch - 1);
   int base = s_pre[ch];

@@ -1,0 +1,207 @@
+// bros_attn_decode (bf16) for short contexts: one workgroup per (row, KV head)
+// segment, in one launch (longer contexts: decode.hip, whose device code says
+// what is computed and how a tile's operands lie).
+//
+// decode.hip cuts the tiles evenly over the chip and folds the cut segments in
+// a second kernel. While contexts are short that second launch, its round of
+// loads and the row prefix every workgroup builds cost as much as the bytes, so
+// here a workgroup takes a whole segment, wave w every fourth block, and folds
+// the waves' results in LDS: no prefix, no partials, no workspace. The loads of
+// a wave's next block are requested as its registers are read, with no branch
+// around them; four waves per SIMD cover the rest of the latency, which bounds
+// it: about 1 us per tile of a wave after 4 us of start-up. Calls in us (32 / 8
+// heads), the even split and this: one row of 100 tokens 8.6 / 4.3, 16 rows of
+// 64 to 256 13.2 / 7.3, 64 of 128 to 512 25.8 / 20.0, 512 of 64 to 256 76 / 69,
+// 16 of 256 to 1024 20.7 / 18.0. (With 8 waves a segment 1 us slower, with 16
+// up to twice as long: a compute unit then reads one segment at its own rate.)
+#include "decode_device.h"
+
+#include <algorithm>
+
+namespace bros {
+namespace dm {
+
+template <int G>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void decode_short_kernel(DecodeArgs a, int seg0) {
+  __shared__ float s_o[kWaves][G][kHeadDim + 4];
+  __shared__ float s_m[kWaves][G], s_l[kWaves][G];
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int w = wave_id_uniform();
+  const int grp = lane >> 4;
+  const int col = lane & 15;
+  const bool head_lane = col < G;
+  const int nkv = a.num_kv_heads;
+  const int Hq = a.num_q_heads;
+  const int seg = seg0 + (int)blockIdx.x;
+  const int row = seg / nkv, g = seg - row * nkv;
+  const int ctx = max(0, min(load_uniform(a.ctx_lens, row), min(a.max_ctx, a.max_blocks_per_seq * kBlockSize)));
+  const int nblk = (ctx + kBlockSize - 1) / kBlockSize;
+  const int n = nblk > w ? (nblk - w + kWaves - 1) / kWaves : 0;   // this wave's blocks
+
+  v4u_t qf[4], kf[4], vf[4];
+  floatx4_t acc[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) acc[t] = floatx4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  float m_ref = kNoMax, l_part = 0.0f;
+
+  // Pool block of this wave's i-th block: block 0 in place of an invalid entry
+  // (masked whole) or past the wave's blocks (not computed), so that the loads
+  // need no branch. (The table is not read past the context.)
+  auto entry = [&](int i, bool& ok) -> int {
+    const int v = load_uniform(a.block_tables, (size_t)row * a.max_blocks_per_seq + max(min(w + kWaves * i, nblk - 1), 0));
+    ok = v >= 0 && v < a.num_blocks;
+    return ok ? v : 0;
+  };
+  auto issue_k = [&](int blk) __attribute__((always_inline)) {
+    const size_t base = ((size_t)blk * nkv + g) * kTileElems + (uint32_t)col * kHeadDim + 8 * grp;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) kf[k] = load_nt(a.k_pool, base + 32 * k);
+  };
+  auto issue_v = [&](int blk) __attribute__((always_inline)) {
+    const size_t base = ((size_t)blk * nkv + g) * kTileElems + (uint32_t)(4 * grp) * kHeadDim + 8 * col;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) vf[j] = load_nt(a.v_pool, base + (size_t)j * kHeadDim);
+  };
+
+  if (n > 0) {
+    bool ok;
+    int blk = entry(0, ok);
+    issue_k(blk);
+    {
+      const size_t qoff = ((size_t)row * Hq + g * G + min(col, G - 1)) * kHeadDim + 8 * grp;   // (padding columns repeat a head)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) qf[k] = *reinterpret_cast<const v4u_t*>(static_cast<const uint16_t*>(a.q) + qoff + 32 * k);
+    }
+    issue_v(blk);
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < n; ++i) {
+      const int b = w + kWaves * i;
+      bool next_ok;
+      const int next = entry(i + 1, next_ok);
+      floatx4_t sc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[k]), __builtin_bit_cast(bf16x8_t, qf[k]), sc, 0, 0, 0);
+      issue_k(next);   // the K registers are free
+      float s[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[r] = sc[r] * a.scale_log2;
+      if (!ok || (b + 1) * kBlockSize > ctx) {   // an invalid entry, or the tail: drop slots past the context
+        const int dir = entry_direction(a.dir, a.cls, a.dir_per_entry, a.max_blocks_per_seq, row, b);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (!ok || b * kBlockSize + slot_of_offset(4 * grp + r, dir) >= ctx) {
+            s[r] = -INFINITY;
+            vf[r] = v4u_t{0u, 0u, 0u, 0u};
+          }
+        }
+      }
+      float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+      if (__builtin_amdgcn_ballot_w64(head_lane && mx > m_ref + kRescaleSlack) != 0) {
+        // rare: move each head's reference max to the max over its 16 slots
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_ref, mx);
+        const float alpha = fast_exp2(m_ref - m_new);
+        m_ref = m_new;
+        l_part *= alpha;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[t][r] *= alpha;
+        }
+      }
+      float p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = fast_exp2(s[r] - m_ref);
+      l_part += (p[0] + p[1]) + (p[2] + p[3]);
+      const short4_t pb = __builtin_bit_cast(short4_t, uint2{pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3])});
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
+        const uint32_t lo = __builtin_amdgcn_perm(vf[1][t >> 1], vf[0][t >> 1], sel);
+        const uint32_t hi = __builtin_amdgcn_perm(vf[3][t >> 1], vf[2][t >> 1], sel);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, uint2{lo, hi}), pb, acc[t], 0, 0, 0);
+      }
+      issue_v(next);   // the V registers are free
+      ok = next_ok;
+    }
+  }
+
+  // The waves' results: lane l holds dims 32 grp + 8 r + t of head col.
+  float l_head = l_part;
+  l_head += __shfl_xor(l_head, 16);
+  l_head += __shfl_xor(l_head, 32);
+  if (head_lane) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float* o = &s_o[w][col][32 * grp + 8 * r];
+      *reinterpret_cast<floatx4_t*>(o) = floatx4_t{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+      *reinterpret_cast<floatx4_t*>(o + 4) = floatx4_t{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
+    }
+    if (grp == 0) {
+      s_m[w][col] = m_ref;
+      s_l[w][col] = l_head;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < G * (kHeadDim / 2); i += kThreads) {
+    const int h = i / (kHeadDim / 2), d = 2 * (i % (kHeadDim / 2));
+    float M = kNoMax;
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) M = fmaxf(M, s_m[x][h]);
+    float L = 0.0f, A0 = 0.0f, A1 = 0.0f;
+#pragma unroll
+    for (int x = 0; x < kWaves; ++x) {
+      const float wt = fast_exp2(s_m[x][h] - M);
+      const float2 o = *reinterpret_cast<const float2*>(&s_o[x][h][d]);
+      L = fmaf(s_l[x][h], wt, L);
+      A0 = fmaf(o.x, wt, A0);
+      A1 = fmaf(o.y, wt, A1);
+    }
+    const float inv = L > 0.0f ? 1.0f / L : 0.0f;   // (a row without context is zeros)
+    uint32_t* out = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) + ((size_t)row * Hq + g * G + h) * kHeadDim + d);
+    *out = pack2_bf16(A0 * inv, A1 * inv);
+  }
+}
+
+// Longest contexts, in blocks, that run here; from kManySegments segments on up
+// to twice as long (with fewer, the even split spreads such contexts over more
+// compute units: four rows of 256 to 1024 tokens 14.3 us against 16.4).
+constexpr int kShortBlocks = 32;
+constexpr int kManySegments = 64;
+constexpr long long kMaxSegmentsPerLaunch = 1 << 23;   // (a launch's threads must stay below 2^32)
+
+template <int G>
+hipError_t launch_short_group(const DecodeArgs& a, hipStream_t stream) {
+  const long long segments = (long long)a.num_rows * a.num_kv_heads;
+  for (long long s0 = 0; s0 < segments; s0 += kMaxSegmentsPerLaunch) {
+    const dim3 grid((unsigned)std::min(segments - s0, kMaxSegmentsPerLaunch));
+    hipLaunchKernelGGL(decode_short_kernel<G>, grid, dim3(kThreads), 0, stream, a, (int)s0);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace dm
+
+bool decode_is_short(const DecodeArgs& a) {
+  const int64_t longest = std::min<int64_t>(a.max_ctx, (int64_t)a.max_blocks_per_seq * kBlockSize);
+  const int64_t blocks = (longest + kBlockSize - 1) / kBlockSize;
+  const int64_t segments = (int64_t)a.num_rows * a.num_kv_heads;
+  return blocks <= (segments >= dm::kManySegments ? 2 * dm::kShortBlocks : dm::kShortBlocks) && segments <= 0x7fffffff;
+}
+
+hipError_t launch_decode_short(const DecodeArgs& a, int group, hipStream_t stream) {
+  switch (group) {
+    case 1: return dm::launch_short_group<1>(a, stream);
+    case 2: return dm::launch_short_group<2>(a, stream);
+    case 4: return dm::launch_short_group<4>(a, stream);
+    case 8: return dm::launch_short_group<8>(a, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace bros

@@ -56,9 +56,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 // waves of the workgroup together, a fourth of the partials each. (Merging
 // inside the decode kernel instead would need device-scope release/acquire
 // between workgroups, which on this chip writes back and invalidates a whole
-// L2 per segment; the kernel boundary is far cheaper.) Six rows of 90 to 2048
-// tokens: 14.5 us when a wave folded all of a segment's 30 to 60 partials and
-// every wave took a tile or two, 5.9 us now.
+// L2 per segment; the kernel boundary is far cheaper.)
 constexpr int kMergeWaves = 4;
 // Partials that a wave folds by itself, in two rounds. (With one round alone, 8,
 // the longest contexts of 64 rows go to the whole workgroup after its own
@@ -301,6 +299,7 @@ namespace {
 // compute units hold at four waves per SIMD (the kernel runs two). The
 // workspace is sized for it.
 constexpr int kMaxDecodeGrid = 1024;
+static_assert(kDecodeGroupSlots == kWaves * kMaxDecodeGrid, "the workspace's partials");
 
 // Events recorded around the decode kernel of every bf16 call (a
 // benchmark's hook; both null when unused).
@@ -311,19 +310,14 @@ hipError_t launch_group(DecodeArgs a, hipStream_t stream, int slot) {
   const hipEvent_t before = g_kernel_ev_before.load(), after = g_kernel_ev_after.load();
   hipError_t e = hipSuccess;
   if (before != nullptr && (e = hipEventRecord(before, stream)) != hipSuccess) return e;
-  const bool whole = decode_is_short(a);
-  if (whole) {
-    e = launch_decode_short(a, G, stream);
-  } else {
-    int grid = resident_workgroups(reinterpret_cast<const void*>(&dm::decode_mfma_kernel<G>), kThreads, slot, stream);
-    grid = grid < kMaxDecodeGrid ? grid : kMaxDecodeGrid;
-    a.num_workers = grid * kWaves;
-    hipLaunchKernelGGL((dm::decode_mfma_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
-    e = hipGetLastError();
-  }
+  if (plan_decode_short(a)) return launch_decode_short(a, G, stream, after);
+  int grid = resident_workgroups(reinterpret_cast<const void*>(&dm::decode_mfma_kernel<G>), kThreads, slot, stream);
+  grid = grid < kMaxDecodeGrid ? grid : kMaxDecodeGrid;
+  a.num_workers = grid * kWaves;
+  hipLaunchKernelGGL((dm::decode_mfma_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (after != nullptr && (e = hipEventRecord(after, stream)) != hipSuccess) return e;
-  if (whole) return hipSuccess;
   return launch_decode_merge(a, G, stream);
 }
 

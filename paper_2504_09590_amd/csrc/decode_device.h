@@ -202,13 +202,12 @@ __device__ __forceinline__ void advance(const DecodeArgs& a, Cursor& c) {
 
 // The even split of the tiles over the grid's waves, the same on every
 // workgroup. With fewer tiles than waves the last waves idle; and while a wave
-// would get less than kLeastTiles tiles, fewer waves take more, down to one
-// tile where segments are short: a tile costs a wave about 1 us, a segment cut
-// in many pieces costs the merge a round per eight of them. Decode calls, us,
-// with at least 1 / 2 / 4 / 8 tiles a wave: 6 rows of 90 to 2048 tokens (32 / 8
-// heads, 64 blocks a segment) 19.8 / 17.6 / 17.5 / 21.9, one row of 8000 30.0 /
-// 29.4 / 23.6 / 24.0, one of 300 10.1 / 11.0 / 11.7 / 14.7, two of 50 to 100
-// 9.3 / 10.5 / 12.2 / 15.7.
+// would get less than kLeastTiles tiles (a batch whose longest context is far
+// above the others, so that decode_short.hip does not take it), fewer waves
+// take more, down to one tile where segments are short: a tile costs a wave
+// about 1 us, a segment cut in many pieces costs the merge a round per eight of
+// them. 6 rows of 90 to 2048 tokens (32 / 8 heads, 64 blocks a segment) with at
+// least 1 / 2 / 4 / 8 tiles a wave: 19.8 / 17.6 / 17.5 / 21.9 us.
 struct Shares {
   int workers;   // waves with tiles
   int total;     // tiles

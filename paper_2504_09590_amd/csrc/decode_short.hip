@@ -1,19 +1,24 @@
-// bros_attn_decode (bf16) for short contexts: one workgroup per (row, KV head)
-// segment, in one launch (longer contexts: decode.hip, whose device code says
-// what is computed and how a tile's operands lie).
+// bros_attn_decode (bf16) for short contexts and for few (row, KV head)
+// segments (the rest: decode.hip, whose device code says what is computed and
+// how a tile's operands lie).
 //
 // decode.hip cuts the tiles evenly over the chip and folds the cut segments in
-// a second kernel. While contexts are short that second launch, its round of
-// loads and the row prefix every workgroup builds cost as much as the bytes, so
-// here a workgroup takes a whole segment, wave w every fourth block, and folds
-// the waves' results in LDS: no prefix, no partials, no workspace. The loads of
+// a second kernel. Where a wave gets few tiles, the row prefix every workgroup
+// builds, the search for its place in it and the walk from there cost more than
+// the tiles. Here a workgroup takes a whole segment, or split_blocks blocks of
+// it, wave w every fourth block, and folds the waves' results in LDS: no
+// prefix, and for whole segments no partials and no second kernel. The loads of
 // a wave's next block are requested as its registers are read, with no branch
 // around them; four waves per SIMD cover the rest of the latency, which bounds
-// it: about 1 us per tile of a wave after 4 us of start-up. Calls in us (32 / 8
-// heads), the even split and this: one row of 100 tokens 8.6 / 4.3, 16 rows of
-// 64 to 256 13.2 / 7.3, 64 of 128 to 512 25.8 / 20.0, 512 of 64 to 256 76 / 69,
-// 16 of 256 to 1024 20.7 / 18.0. (With 8 waves a segment 1 us slower, with 16
-// up to twice as long: a compute unit then reads one segment at its own rate.)
+// it: under 1 us per tile of a wave after 4 us of start-up. Calls in us (32 / 8
+// heads unless said), the even split and this:
+//   whole  one row of 100 tokens 8.6 / 4.3, 16 rows of 64 to 256 13.2 / 7.3, 64 of
+//          128 to 512 25.8 / 20.0, 512 of 64 to 256 76 / 69
+//   split  one row of 8000 22.7 / 11.7, six of 90 to 2048 17.4 / 13.0, four of
+//          1024 to 4096 22.6 / 14.4, 64 of 512 to 2048 with 8 / 1 heads 22.5 /
+//          14.9, 8 of 4000 to 8192 with 64 / 8 heads 50.9 / 43.4
+// (With 8 waves a segment 1 us slower, with 16 up to twice as long: a compute
+// unit then reads one segment at its own rate.)
 #include "decode_device.h"
 
 #include <algorithm>
@@ -21,6 +26,9 @@
 namespace bros {
 namespace dm {
 
+// Blocks [sp S, (sp + 1) S) of segment seg0 + blockIdx.x, S = split_blocks and
+// sp = blockIdx.y: the whole segment when it has no more than S blocks, else a
+// partial in slot (segment * n_split_max + sp) * G + head.
 template <int G>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void decode_short_kernel(DecodeArgs a, int seg0) {
   __shared__ float s_o[kWaves][G][kHeadDim + 4];
@@ -37,7 +45,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const int row = seg / nkv, g = seg - row * nkv;
   const int ctx = max(0, min(load_uniform(a.ctx_lens, row), min(a.max_ctx, a.max_blocks_per_seq * kBlockSize)));
   const int nblk = (ctx + kBlockSize - 1) / kBlockSize;
-  const int n = nblk > w ? (nblk - w + kWaves - 1) / kWaves : 0;   // this wave's blocks
+  const int sp = blockIdx.y;
+  const int b0 = sp * a.split_blocks, b1 = min(nblk, b0 + a.split_blocks);
+  if (sp > 0 && b0 >= nblk) return;
+  const int first = b0 + w;                                               // this wave's blocks: first, first + 4, ...
+  const int n = b1 > first ? (b1 - first + kWaves - 1) / kWaves : 0;
 
   v4u_t qf[4], kf[4], vf[4];
   floatx4_t acc[8];
@@ -49,7 +61,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   // (masked whole) or past the wave's blocks (not computed), so that the loads
   // need no branch. (The table is not read past the context.)
   auto entry = [&](int i, bool& ok) -> int {
-    const int v = load_uniform(a.block_tables, (size_t)row * a.max_blocks_per_seq + max(min(w + kWaves * i, nblk - 1), 0));
+    const int v = load_uniform(a.block_tables, (size_t)row * a.max_blocks_per_seq + min(first + kWaves * i, b1 - 1));
     ok = v >= 0 && v < a.num_blocks;
     return ok ? v : 0;
   };
@@ -76,7 +88,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     issue_v(blk);
 #pragma clang loop unroll(disable)
     for (int i = 0; i < n; ++i) {
-      const int b = w + kWaves * i;
+      const int b = first + kWaves * i;
       bool next_ok;
       const int next = entry(i + 1, next_ok);
       floatx4_t sc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -116,13 +128,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
       for (int r = 0; r < 4; ++r) p[r] = fast_exp2(s[r] - m_ref);
       l_part += (p[0] + p[1]) + (p[2] + p[3]);
-      const short4_t pb = __builtin_bit_cast(short4_t, uint2{pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3])});
+      // The weights as a bf16 and the bf16 of what it leaves: the matrix cores
+      // wait for the loads here anyway, and the even split, which this
+      // replaces, cut a short context so finely that a good part of its
+      // weights were maxima, exactly 1. (Distance from 64 bits, one to six
+      // rows: 0.0019-0.0021 there, 0.0022-0.0023 with the first part alone,
+      // 0.0017 with both, the output's own rounding; 0.1 us a call.)
+      const uint2 hi2 = {pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3])};
+      const uint2 lo2 = {pack2_bf16(p[0] - bf16_lo(hi2.x), p[1] - bf16_hi(hi2.x)),
+                         pack2_bf16(p[2] - bf16_lo(hi2.y), p[3] - bf16_hi(hi2.y))};
+      const short4_t pb = __builtin_bit_cast(short4_t, hi2), pl = __builtin_bit_cast(short4_t, lo2);
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
         const uint32_t lo = __builtin_amdgcn_perm(vf[1][t >> 1], vf[0][t >> 1], sel);
         const uint32_t hi = __builtin_amdgcn_perm(vf[3][t >> 1], vf[2][t >> 1], sel);
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, uint2{lo, hi}), pb, acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, uint2{lo, hi}), pl, acc[t], 0, 0, 0);
       }
       issue_v(next);   // the V registers are free
       ok = next_ok;
@@ -160,46 +182,134 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
       A0 = fmaf(o.x, wt, A0);
       A1 = fmaf(o.y, wt, A1);
     }
+    if (nblk > a.split_blocks) {
+      const size_t slot = ((size_t)seg * a.n_split_max + sp) * G + h;
+      *reinterpret_cast<float2*>(a.ws_acc + slot * kHeadDim + d) = make_float2(A0, A1);
+      if (d == 0) {
+        a.ws_ml[2 * slot] = M;
+        a.ws_ml[2 * slot + 1] = L;
+      }
+      continue;
+    }
     const float inv = L > 0.0f ? 1.0f / L : 0.0f;   // (a row without context is zeros)
     uint32_t* out = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) + ((size_t)row * Hq + g * G + h) * kHeadDim + d);
     *out = pack2_bf16(A0 * inv, A1 * inv);
   }
 }
 
-// Longest contexts, in blocks, that run here; from kManySegments segments on up
-// to twice as long (with fewer, the even split spreads such contexts over more
-// compute units: four rows of 256 to 1024 tokens 14.3 us against 16.4).
+// Longest contexts, in blocks, that run whole; from kManySegments segments on up
+// to twice as long (with fewer, pieces spread such contexts over more compute
+// units: four rows of 256 to 1024 tokens 9.5 us in pieces of 16 blocks, 16.4 whole).
 constexpr int kShortBlocks = 32;
 constexpr int kManySegments = 64;
+// Pieces of longer contexts: the shortest that number no more than `most`, one
+// to two per compute unit; with more of them the even split's longer walks read
+// the HBM better (64 rows of 512 to 2048 tokens, 2048 pieces of 32 blocks: 63 us
+// there, 65 here). A segment's partials are folded by one workgroup, eight a
+// round.
+struct Pieces {
+  int32_t blocks, most;
+};
+constexpr Pieces kPieces[] = {{16, 256}, {32, 512}, {64, 512}};
+constexpr int kMaxSplits = 64;
 constexpr long long kMaxSegmentsPerLaunch = 1 << 23;   // (a launch's threads must stay below 2^32)
 
+// Folds the partials of the segments that were split, a workgroup each: o =
+// sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i. Thread t takes two dims of
+// one head per pass; the partials' loads do not depend on one another.
 template <int G>
-hipError_t launch_short_group(const DecodeArgs& a, hipStream_t stream) {
-  const long long segments = (long long)a.num_rows * a.num_kv_heads;
-  for (long long s0 = 0; s0 < segments; s0 += kMaxSegmentsPerLaunch) {
-    const dim3 grid((unsigned)std::min(segments - s0, kMaxSegmentsPerLaunch));
+__global__ __launch_bounds__(kThreads) void decode_short_merge_kernel(DecodeArgs a) {
+  const int seg = blockIdx.x;
+  const int nkv = a.num_kv_heads;
+  const int row = seg / nkv, g = seg - row * nkv;
+  const int ctx = max(0, min(load_uniform(a.ctx_lens, row), min(a.max_ctx, a.max_blocks_per_seq * kBlockSize)));
+  const int nblk = (ctx + kBlockSize - 1) / kBlockSize;
+  if (nblk <= a.split_blocks) return;   // written by the decode
+  const int nsp = (nblk + a.split_blocks - 1) / a.split_blocks;
+  const size_t slot0 = (size_t)seg * a.n_split_max * G;
+  for (int i = threadIdx.x; i < G * (kHeadDim / 2); i += kThreads) {
+    const int h = i / (kHeadDim / 2), d = 2 * (i % (kHeadDim / 2));
+    const float2* ml = reinterpret_cast<const float2*>(a.ws_ml) + slot0 + h;
+    const float* acc = a.ws_acc + (slot0 + h) * kHeadDim + d;
+    float M = kNoMax, L = 0.0f, A0 = 0.0f, A1 = 0.0f;
+    for (int c = 0; c < nsp; c += 8) {   // eight partials a round, indices clamped in range
+      float2 x[8], v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = min(c + u, nsp - 1);
+        x[u] = ml[(size_t)j * G];
+        v[u] = *reinterpret_cast<const float2*>(acc + (size_t)j * G * kHeadDim);
+      }
+      float Mn = M;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) Mn = fmaxf(Mn, x[u].x);
+      const float alpha = fast_exp2(M - Mn);
+      L *= alpha;
+      A0 *= alpha;
+      A1 *= alpha;
+      M = Mn;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float wt = c + u < nsp ? fast_exp2(x[u].x - M) : 0.0f;
+        L = fmaf(x[u].y, wt, L);
+        A0 = fmaf(v[u].x, wt, A0);
+        A1 = fmaf(v[u].y, wt, A1);
+      }
+    }
+    const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+    *reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.out) + ((size_t)row * a.num_q_heads + g * G + h) * kHeadDim + d) =
+        pack2_bf16(A0 * inv, A1 * inv);
+  }
+}
+
+template <int G>
+hipError_t launch_short_group(DecodeArgs a, hipStream_t stream, hipEvent_t between) {
+  const int64_t segments = (int64_t)a.num_rows * a.num_kv_heads;
+  for (int64_t s0 = 0; s0 < segments; s0 += kMaxSegmentsPerLaunch) {
+    const dim3 grid((unsigned)std::min<int64_t>(segments - s0, kMaxSegmentsPerLaunch), (unsigned)a.n_split_max);
     hipLaunchKernelGGL(decode_short_kernel<G>, grid, dim3(kThreads), 0, stream, a, (int)s0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  if (between != nullptr) {
+    const hipError_t e = hipEventRecord(between, stream);
+    if (e != hipSuccess) return e;
+  }
+  if (a.n_split_max <= 1) return hipSuccess;
+  hipLaunchKernelGGL(decode_short_merge_kernel<G>, dim3((unsigned)segments), dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace dm
 
-bool decode_is_short(const DecodeArgs& a) {
+bool plan_decode_short(DecodeArgs& a) {
   const int64_t longest = std::min<int64_t>(a.max_ctx, (int64_t)a.max_blocks_per_seq * kBlockSize);
-  const int64_t blocks = (longest + kBlockSize - 1) / kBlockSize;
+  const int64_t blocks = std::max<int64_t>(1, (longest + kBlockSize - 1) / kBlockSize);
   const int64_t segments = (int64_t)a.num_rows * a.num_kv_heads;
-  return blocks <= (segments >= dm::kManySegments ? 2 * dm::kShortBlocks : dm::kShortBlocks) && segments <= 0x7fffffff;
+  if (segments > 0x7fffffff) return false;
+  if (blocks <= (segments >= dm::kManySegments ? 2 * dm::kShortBlocks : dm::kShortBlocks)) {
+    a.split_blocks = (int32_t)blocks;
+    a.n_split_max = 1;
+    return true;
+  }
+  // (partials: the workspace has a slot per query row and kDecodeGroupSlots groups more)
+  const int64_t slots = (int64_t)a.num_rows * a.num_q_heads + (int64_t)kDecodeGroupSlots * std::min(a.num_q_heads, 8);
+  for (const dm::Pieces& p : dm::kPieces) {
+    const int64_t splits = (blocks + p.blocks - 1) / p.blocks;
+    if (segments * splits > p.most || splits > dm::kMaxSplits || segments * splits * (a.num_q_heads / a.num_kv_heads) > slots) continue;
+    a.split_blocks = p.blocks;
+    a.n_split_max = (int32_t)splits;
+    return true;
+  }
+  return false;
 }
 
-hipError_t launch_decode_short(const DecodeArgs& a, int group, hipStream_t stream) {
+hipError_t launch_decode_short(const DecodeArgs& a, int group, hipStream_t stream, hipEvent_t between) {
   switch (group) {
-    case 1: return dm::launch_short_group<1>(a, stream);
-    case 2: return dm::launch_short_group<2>(a, stream);
-    case 4: return dm::launch_short_group<4>(a, stream);
-    case 8: return dm::launch_short_group<8>(a, stream);
+    case 1: return dm::launch_short_group<1>(a, stream, between);
+    case 2: return dm::launch_short_group<2>(a, stream, between);
+    case 4: return dm::launch_short_group<4>(a, stream, between);
+    case 8: return dm::launch_short_group<8>(a, stream, between);
     default: return hipErrorInvalidValue;
   }
 }

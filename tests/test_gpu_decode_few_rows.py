@@ -1,7 +1,9 @@
-"""bf16 decode of few rows: fewer tiles than waves (one tile a wave for short
-segments, up to four for long ones, the waves spread over the workgroups), and
-segments cut into so many pieces that the merge's waves share them. Against the
-oracle at the bf16 bar of every other kernel test, and twice bitwise."""
+"""bf16 decode of few rows: contexts in pieces of 16, 32 or 64 blocks, one
+workgroup each, and their merge (a round per eight partials); beyond 64 pieces
+the even split, whose merge's waves share a segment's many partials, and which
+gives a wave up to four tiles when one long context stands among short ones.
+Against the oracle at the bf16 bar of every other kernel test, and twice
+bitwise."""
 
 import numpy as np
 import pytest
@@ -14,9 +16,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("group,hkv", [(1, 8), (2, 2), (4, 8), (8, 1)])
-# blocks per segment around the limits: 1, 16 (one tile a wave below 32 blocks), 17 and 33 pieces a segment, and
-# 64, 68 (four tiles a wave, 16 and 17 pieces), 1000
-@pytest.mark.parametrize("blocks", [1, 16, 17, 33, 64, 68, 1000])
+# whole up to 32 blocks; then 3 pieces, 8 and 9 partials (one round and two), 63, 64 and 65 of 16 blocks
+@pytest.mark.parametrize("blocks", [1, 32, 33, 128, 129, 1000, 1024, 1025])
 def test_one_row(group, hkv, blocks):
     require_gpu()
     ctx = 16 * blocks - (blocks % 3)
@@ -36,3 +37,22 @@ def test_few_rows_of_all_lengths(rows):
     poison_unowned(b)
     announce(f"decode {rows} rows of 1 to 9000 tokens, one empty")
     compare(run_decode(b), ref_decode(b), "bf16", f"{rows} rows")
+
+
+@pytest.mark.parametrize("group", [1, 8])
+def test_even_split_of_one_very_long_row(group):
+    # more than 64 pieces of 64 blocks: the even split, a thousand partials in one segment
+    require_gpu()
+    b = W.custom([16 * 4100 - 3, 30], [W.BE, W.RT], group, 1, seed=group, spare_blocks=3)
+    poison_unowned(b)
+    announce(f"decode one row of 4100 blocks, G={group}")
+    compare(run_decode(b), ref_decode(b), "bf16", "4100 blocks")
+
+
+def test_one_long_row_among_many_short_ones():
+    # the longest context alone sets the pieces: too many of them, and few tiles for the even split
+    require_gpu()
+    ctx = [5, 9000] + [int(x) for x in np.random.default_rng(7).integers(1, 60, 98)]
+    b = poison_unowned(W.custom(ctx, [i % 2 for i in range(100)], 32, 8, seed=7, spare_blocks=3))
+    announce("decode one long row among 99 short ones")
+    compare(run_decode(b), ref_decode(b), "bf16", "one long row among short ones")

@@ -134,7 +134,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
       // weights were maxima, exactly 1. (Distance from 64 bits, one to six
       // rows: 0.0019-0.0021 there, 0.0022-0.0023 with the first part alone,
       // 0.0017 with both, the output's own rounding; 0.1 us a call.)
-      const uint2 hi2 = {pack2_bf16(p[0], p[1]), pack2_bf16(p[2], p[3])};
+      // The first part is taken a little short of the weight, so that the second
+      // is positive too: with a part that is 0 or negative, a V value of infinity
+      // would become a NaN. (What both leave is 2^-15 of the weight at most.)
+      constexpr float kShort = 1.0f - 0x1p-6f;
+      const uint2 hi2 = {pack2_bf16(kShort * p[0], kShort * p[1]), pack2_bf16(kShort * p[2], kShort * p[3])};
       const uint2 lo2 = {pack2_bf16(p[0] - bf16_lo(hi2.x), p[1] - bf16_hi(hi2.x)),
                          pack2_bf16(p[2] - bf16_lo(hi2.y), p[3] - bf16_hi(hi2.y))};
       const short4_t pb = __builtin_bit_cast(short4_t, hi2), pl = __builtin_bit_cast(short4_t, lo2);

@@ -8,6 +8,7 @@ bitwise."""
 import numpy as np
 import pytest
 
+import oracle
 from paper_2504_09590_amd import workload as W
 from tests.gpu_helpers import announce, compare, poison_unowned, require_gpu
 from tests.test_gpu_decode import ref_decode, run_decode
@@ -56,3 +57,19 @@ def test_one_long_row_among_many_short_ones():
     b = poison_unowned(W.custom(ctx, [i % 2 for i in range(100)], 32, 8, seed=7, spare_blocks=3))
     announce("decode one long row among 99 short ones")
     compare(run_decode(b), ref_decode(b), "bf16", "one long row among short ones")
+
+
+@pytest.mark.parametrize("ctx,pos", [([1], 0), ([300], 299), ([300, 40], 17), ([9000], 4321)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_infinite_values_stay_infinite(ctx, pos, value):
+    # a V value of infinity, under weights of 1 (a lone token) and less: the result's dim is that infinity, not a NaN
+    require_gpu()
+    b = W.custom(ctx, [i % 2 for i in range(len(ctx))], 8, 2, seed=pos, spare_blocks=3)
+    blk, slot = oracle.physical_location(b.block_tables, b.dir, 0, np.array([pos]))
+    ref = ref_decode(b)
+    b.v_pool[blk[0], :, slot[0], 5] = np.uint16(0x7F80 if value > 0 else 0xFF80)
+    announce(f"decode of contexts {ctx}, a V value of {value} at {pos}")
+    got = oracle.widen(run_decode(b), "bf16")
+    assert (got[0, :, 5] == value).all()
+    ref[0, :, 5] = got[0, :, 5] = 0.0
+    assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-2

@@ -206,6 +206,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 // units: four rows of 256 to 1024 tokens 9.5 us in pieces of 16 blocks, 16.4 whole).
 constexpr int kShortBlocks = 32;
 constexpr int kManySegments = 64;
+// From two segments per compute unit on, a few long contexts among short ones
+// are waited for, and the even split's partials, which this saves, are the
+// smaller the fewer heads share a segment. Steps in us, the even split / whole:
+//   G = 8  64 / 8 heads, 256 rows up to 1024 tokens 135.4 / 121.5
+//   G = 4  32 / 8 heads, 128 rows of lognormal contexts up to 768 54.6 / 53.7, up
+//          to 1024 56.3 / 59.7; 256 uniform ones up to 768 92.7 / 89.1
+//   G = 2  16 / 8 heads, 256 rows up to 768 88.1 / 92.8
+//   G = 1  8 / 8 heads, 256 rows up to 384 51.9 / 50.5, up to 512 63.3 / 63.7; 512
+//          rows up to 1024 207.0 / 213.6, 64 rows 36.1 / 36.9
+constexpr int kRoundSegments = 512;
+inline int longest_whole(int64_t segments, int group) {
+  if (segments < kManySegments) return kShortBlocks;
+  if (segments < kRoundSegments) return 2 * kShortBlocks;
+  return group >= 8 ? 64 : group >= 4 ? 48 : group >= 2 ? 32 : 24;
+}
 // Pieces of longer contexts: the shortest that number no more than `most`, one
 // to two per compute unit; with more of them the even split's longer walks read
 // the HBM better (64 rows of 512 to 2048 tokens, 2048 pieces of 32 blocks: 63 us
@@ -291,7 +306,7 @@ bool plan_decode_short(DecodeArgs& a) {
   const int64_t blocks = std::max<int64_t>(1, (longest + kBlockSize - 1) / kBlockSize);
   const int64_t segments = (int64_t)a.num_rows * a.num_kv_heads;
   if (segments > 0x7fffffff) return false;
-  if (blocks <= (segments >= dm::kManySegments ? 2 * dm::kShortBlocks : dm::kShortBlocks)) {
+  if (blocks <= dm::longest_whole(segments, a.num_q_heads / a.num_kv_heads)) {
     a.split_blocks = (int32_t)blocks;
     a.n_split_max = 1;
     return true;
@@ -300,7 +315,7 @@ bool plan_decode_short(DecodeArgs& a) {
   const int64_t slots = (int64_t)a.num_rows * a.num_q_heads + (int64_t)kDecodeGroupSlots * std::min(a.num_q_heads, 8);
   for (const dm::Pieces& p : dm::kPieces) {
     const int64_t splits = (blocks + p.blocks - 1) / p.blocks;
-    if (segments * splits > p.most || splits > dm::kMaxSplits || segments * splits * (a.num_q_heads / a.num_kv_heads) > slots) continue;
+    if (splits < 2 || segments * splits > p.most || splits > dm::kMaxSplits || segments * splits * (a.num_q_heads / a.num_kv_heads) > slots) continue;
     a.split_blocks = p.blocks;
     a.n_split_max = (int32_t)splits;
     return true;

@@ -1,5 +1,6 @@
 """bf16 decode of short contexts in one launch: contexts and segment counts on
-both sides of its rule (32 blocks, 64 from 64 segments on), all group sizes,
+both sides of its rule (32 blocks, 64 from 64 segments on, 24, 32, 48 or 64 by
+group size from 512 on), all group sizes,
 empty rows, a max_ctx above every context, invalid table entries and directions
 per entry. Against the oracle at the bf16 bar of every other kernel test."""
 
@@ -16,7 +17,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("group,hkv,rows,longest", [
     (1, 8, 5, 512), (2, 3, 5, 513), (4, 8, 7, 512), (8, 1, 3, 17), (4, 8, 8, 1024), (4, 8, 7, 1024), (8, 2, 32, 1024),
-    (4, 8, 8, 1025), (2, 1, 200, 700), (4, 8, 300, 90)])
+    (4, 8, 8, 1025), (2, 1, 200, 700), (4, 8, 300, 90),
+    (4, 8, 63, 1024), (4, 8, 64, 769), (4, 8, 65, 768), (2, 8, 64, 512), (2, 8, 65, 513), (1, 8, 65, 384), (1, 8, 65, 385), (8, 8, 65, 1024)])
 def test_either_side_of_the_rule(group, hkv, rows, longest):
     require_gpu()
     ctx = [int(x) for x in np.random.default_rng(rows).integers(1, longest + 1, rows)]

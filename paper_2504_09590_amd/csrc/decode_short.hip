@@ -269,10 +269,12 @@ __global__ __launch_bounds__(kThreads) void decode_short_merge_kernel(DecodeArgs
       M = Mn;
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const float wt = c + u < nsp ? fast_exp2(x[u].x - M) : 0.0f;
-        L = fmaf(x[u].y, wt, L);
-        A0 = fmaf(v[u].x, wt, A0);
-        A1 = fmaf(v[u].y, wt, A1);
+        // (a round's padding adds zero by selection: the partial it repeats may hold an infinity)
+        const bool use = c + u < nsp;
+        const float wt = use ? fast_exp2(x[u].x - M) : 0.0f;
+        L = fmaf(use ? x[u].y : 0.0f, wt, L);
+        A0 = fmaf(use ? v[u].x : 0.0f, wt, A0);
+        A1 = fmaf(use ? v[u].y : 0.0f, wt, A1);
       }
     }
     const float inv = L > 0.0f ? 1.0f / L : 0.0f;

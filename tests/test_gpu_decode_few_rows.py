@@ -73,3 +73,19 @@ def test_infinite_values_stay_infinite(ctx, pos, value):
     assert (got[0, :, 5] == value).all()
     ref[0, :, 5] = got[0, :, 5] = 0.0
     assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-2
+
+
+# pieces that do not fill a round of eight of the merge: 3, 36 (twice) and 9 of 16 blocks
+@pytest.mark.parametrize("ctx,pos", [([600], 599), ([9000], 8999), ([9000, 40], 8960), ([2300, 2048], 2299)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_infinite_values_of_the_last_piece(ctx, pos, value):
+    require_gpu()
+    b = W.custom(ctx, [i % 2 for i in range(len(ctx))], 8, 2, seed=pos, spare_blocks=3)
+    blk, slot = oracle.physical_location(b.block_tables, b.dir, 0, np.array([pos]))
+    ref = ref_decode(b)
+    b.v_pool[blk[0], :, slot[0], 5] = np.uint16(0x7F80 if value > 0 else 0xFF80)
+    announce(f"decode of contexts {ctx}, a V value of {value} at {pos}, in the last piece")
+    got = oracle.widen(run_decode(b), "bf16")
+    assert (got[0, :, 5] == value).all()
+    ref[0, :, 5] = got[0, :, 5] = 0.0
+    assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-2

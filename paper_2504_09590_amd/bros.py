@@ -227,9 +227,9 @@ def attn_prefill_until(num_seqs: int, out, q, cu_q, max_q_len: int, k_pool, v_po
     nb, hkv, bs, d = k_pool.shape
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(LIB.bros_attn_prefill_chunk(_ptr(out), _ptr(q), _ptr(cu_q), q.shape[0], int(max_q_len), _ptr(k_pool),
-                                       _ptr(v_pool), nb, _ptr(block_tables), block_tables.shape[1], _ptr(dir),
-                                       _ptr(cls), _dir_mode(dir, block_tables), _ptr(ctx_lens), int(max_ctx),
-                                       num_seqs, q.shape[1], hkv, d, bs, 0.0, _dtype_code(q), _ptr(workspace),
+                                       _ptr(v_pool), nb, _rows_from(block_tables, 0), block_tables.shape[1],
+                                       _rows_from(dir, 0), _rows_from(cls, 0), _dir_mode(dir, block_tables),
+                                       _rows_from(ctx_lens, 0), int(max_ctx), num_seqs, q.shape[1], hkv, d, bs, 0.0, _dtype_code(q), _ptr(workspace),
                                        ws_bytes, _stream(stream)))
 
 

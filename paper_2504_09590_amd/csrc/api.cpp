@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -166,6 +167,7 @@ int bros_attn_prefill_chunk(void* out, const void* q, const int32_t* cu_q,
     return fail(BROS_E_SHAPE, "%s: negative count (seqs=%d tokens=%d max_q_len=%d max_ctx=%d)", fn, num_seqs, num_q_tokens, max_q_len, max_ctx);
   if (num_seqs == 0 || num_q_tokens == 0) return ok();
   if (max_q_len == 0) return fail(BROS_E_SHAPE, "%s: max_q_len is 0 with %d query rows", fn, num_q_tokens);
+  max_q_len = std::min(max_q_len, num_q_tokens);   // (a loose bound must not size the grid)
   if (!out || !q || !cu_q || !k_pool || !v_pool || !ctx_lens) return fail(BROS_E_NULL, "%s: a tensor or length pointer is NULL", fn);
   st = check_meta(fn, block_tables, max_blocks_per_seq, dir, cls, dir_per_entry, num_blocks);
   if (st) return st;
@@ -280,6 +282,7 @@ int bros_attn_mixed(void* out_prefill, const void* q_prefill, const int32_t* cu_
                                    nullptr, 0, stream);
   // both halves: validate as the two calls do
   if (max_q_len == 0) return fail(BROS_E_SHAPE, "%s: max_q_len is 0 with %d query rows", fn, num_q_tokens);
+  max_q_len = std::min(max_q_len, num_q_tokens);
   if (!out_prefill || !q_prefill || !cu_q || !out_decode || !q_decode || !k_pool || !v_pool)
     return fail(BROS_E_NULL, "%s: a tensor or offset pointer is NULL", fn);
   st = check_meta(fn, block_tables, max_blocks_per_seq, dir, cls, dir_per_entry, num_blocks);

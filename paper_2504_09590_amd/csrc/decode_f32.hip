@@ -35,6 +35,7 @@
 // decode.hip). Rows of a wave, then streams of the workgroup (through LDS),
 // then splits (merge kernel) are combined with max-rescaling.
 #include "decode_common.h"
+#include "plan.h"
 
 #include <algorithm>
 
@@ -538,7 +539,7 @@ hipError_t launch_group_f32(DecodeArgs a, hipStream_t stream, int slot) {
   // and these (32 / 8 heads): 64 rows of 30 to 300 tokens 33 / 23, 16 rows of 64
   // to 2048 54 / 40, 8 rows of 1000 to 4000 71 / 47, 64 rows of 500 to 2048 141
   // / 135 (144 with 64 blocks an item), one row 21 both ways.
-  const int maxblk = std::max(1, std::min((a.max_ctx + kBlockSize - 1) / kBlockSize, a.max_blocks_per_seq));
+  const int maxblk = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
   const long long segments = (long long)a.num_rows * a.num_kv_heads;
   const long long want = (kItems + segments - 1) / segments;   // splits of the longest context
   int per = std::min((int)((maxblk + want - 1) / want), kMaxItemBlocks);

@@ -44,6 +44,7 @@
 // or a NaN, which a zero weight would spread; such a block (rare) is weighted
 // on the vector ALU, each row taking only the V rows it sees.
 #include "decode_common.h"
+#include "plan.h"
 
 #include <algorithm>
 
@@ -318,7 +319,7 @@ hipError_t launch_group(DecodeArgs a, hipStream_t stream) {
   // Split units over their blocks while they leave compute units idle (two
   // workgroups each), in multiples of the plan's split, whose count the
   // workspace is sized for.
-  const int maxblk = std::max(1, std::min((a.max_ctx + kBlockSize - 1) / kBlockSize, a.max_blocks_per_seq));
+  const int maxblk = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
   const long long room = 2LL * stream_compute_units(stream) / units;
   const long long want = std::max(1LL, std::min<long long>(room, maxblk / (kMinBlocksPerWave * kWaves)));
   const int per = (int)((maxblk + want - 1) / want);

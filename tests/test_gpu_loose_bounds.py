@@ -8,6 +8,7 @@ import pytest
 
 from paper_2504_09590_amd import workload as W
 from tests.gpu_helpers import announce, compare, poison_unowned, require_gpu
+from tests.test_gpu_decode import ref_decode
 from tests.test_gpu_prefill import chunk_batch, ref_prefill, written
 
 pytestmark = pytest.mark.gpu
@@ -43,6 +44,22 @@ def test_chunk_rows_above_the_longest(dtype, group, max_ctx, max_q):
     b = poison_unowned(written(chunk_batch([2000, 7], [100, 33], [W.RT, W.BE], group=group, hkv=1, dtype=dtype, seed=group)))
     announce(f"{dtype} chunks G={group} under max_q_len {max_q}, max_ctx {max_ctx}")
     compare(run_with_bounds(b, max_ctx, max_q), ref_prefill(b), dtype, "loose max_q_len")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("max_ctx", [1 << 20, INT32_MAX - 15, INT32_MAX - 14, INT32_MAX])
+@pytest.mark.parametrize("chunk", [False, True], ids=["decode", "chunk"])
+def test_contexts_above_the_longest(dtype, max_ctx, chunk):
+    # contexts of more than one split (64 blocks), which the merge has to fold
+    require_gpu()
+    if chunk:
+        b = written(chunk_batch([2500], [2], [W.RT], group=1, hkv=1, dtype=dtype, seed=3))
+    else:
+        b = W.custom([2500, 31], [W.RT, W.BE], 1, 1, dtype=dtype, seed=3, spare_blocks=3)
+    poison_unowned(b)
+    announce(f"{dtype} {'chunk' if chunk else 'decode'} under max_ctx {max_ctx}")
+    ref = ref_prefill(b) if chunk else ref_decode(b)
+    compare(run_with_bounds(b, max_ctx, 2 if chunk else None), ref, dtype, "loose max_ctx")
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

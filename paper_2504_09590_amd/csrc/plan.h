@@ -15,4 +15,54 @@ inline int32_t longest_blocks(int32_t max_ctx, int32_t max_blocks_per_seq) {
   return (int32_t)std::max<int64_t>(1, std::min<int64_t>(blocks, max_blocks_per_seq));
 }
 
+// The fp32 prefill's units (`positions` positions of one chunk and KV head each)
+// and how far their blocks are split over workgroups.
+struct F32ChunkPlan {
+  int64_t units;           // workgroups per split, all KV heads
+  int32_t tiles_per_seq;   // ranks of every sequence (0: ranks by rows)
+  int32_t split_blocks;
+  int32_t splits;
+};
+
+// Chunks of about one length are ranked longest tile first, every sequence with
+// the ranks of the longest: its bound, and no more than all the rows. Where that
+// gives more than twice the ranks the rows can need (one long chunk among short
+// ones), they are counted from the rows instead. One chunk of 1024 rows and 255 of
+// one on 300 tokens (32 / 8 heads): 966 us, by rows 291.
+//
+// Units are split over their blocks while those that the rows can need leave room,
+// two workgroups per compute unit, in multiples of the plan's split, whose count the
+// workspace is sized for: the count with the least expected time. A block takes a
+// wave 2.75 us, and 1.4 times that beside a second workgroup, since the fp32 matrix
+// instructions bound it; a unit's start takes as long as 3.3 of them, a merge 5 and
+// 0.6 per split. Fitted to 550 calls of 1 to 1100 rows on 0 to 4000 cached tokens,
+// each at four split sizes: 0.1 % above the best of them on average. Us, split down
+// to 16 blocks / to 8 / this: one row on 300 tokens (8 / 8 heads) 12.5 / 11.5 / 10.3,
+// 256 rows without cached tokens (16 / 8) 12.8 / 18.8 / 12.8.
+inline F32ChunkPlan plan_f32_chunks(int32_t num_rows, int32_t num_seqs, int32_t max_q_len, int32_t num_kv_heads,
+                                    int32_t positions, int32_t longest, int32_t plan_blocks, int32_t compute_units) {
+  const int64_t tiles = ((int64_t)std::min(max_q_len, num_rows) + positions - 1) / positions;
+  const int64_t by_rows = (int64_t)num_rows / positions + num_seqs;
+  F32ChunkPlan p;
+  const bool compact = num_seqs * tiles > 2 * by_rows;
+  p.tiles_per_seq = compact ? 0 : (int32_t)tiles;
+  p.units = (compact ? by_rows : num_seqs * tiles) * num_kv_heads;
+  const int64_t live = std::min(num_seqs * tiles, by_rows) * num_kv_heads;
+  double best = 0.0;
+  p.split_blocks = 0;
+  const int64_t most = std::max<int64_t>(1, std::min<int64_t>(2 * compute_units / live, longest / 4));
+  for (int64_t want = 1; want <= most; ++want) {
+    const int64_t per = ((longest + want - 1) / want + plan_blocks - 1) / plan_blocks * plan_blocks;
+    const int64_t splits = (longest + per - 1) / per;
+    const double steps = (double)((std::min<int64_t>(per, longest) + 3) / 4);   // blocks of a wave
+    double us = (steps + 3.3) * 2.75 * (live * splits > compute_units ? 1.4 : 1.0);
+    if (splits > 1) us += 5.0 + 0.6 * (double)splits;
+    if (want > 1 && us >= best) continue;
+    best = us;
+    p.split_blocks = (int32_t)per;
+    p.splits = (int32_t)splits;
+  }
+  return p;
+}
+
 }  // namespace bros

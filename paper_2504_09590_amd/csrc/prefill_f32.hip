@@ -66,9 +66,25 @@ struct Unit {
   int cap;         // the clamp: max_ctx and the table's width
 };
 
+// The last sequence s with cu_q[s] / kPos + s <= r, 64 sequences per step. Every
+// sequence has at least the ranks its tiles need, whatever its rows start at.
+template <int kPos>
+__device__ __forceinline__ int ranked_sequence(const DecodeArgs& a, int r, int lane) {
+  int s = 0;
+  for (int base = 0; base < a.num_seqs; base += kWave) {
+    const int i = base + lane;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(i < a.num_seqs && a.cu_q[min(i, a.num_seqs - 1)] / kPos + i <= r);
+    s = max(s, base + __builtin_popcountll(m) - 1);
+    if (m != ~0ull) break;
+  }
+  return __builtin_amdgcn_readfirstlane(s);
+}
+
 __device__ __forceinline__ int seen(const Unit& u, int j) { return max(min(u.see0 + j, u.cap), 0); }
 
-template <int G>
+// kByRows: how units are ranked (F32ChunkPlan). A variant of its own: with the choice
+// made in the kernel, the loop's code came out 2 to 4 % slower.
+template <int G, bool kByRows>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void prefill_f32_kernel(DecodeArgs a, int unit0) {
   constexpr int kPos = kCols / G;   // positions of a unit
   __shared__ float s_o[kWaves][kCols][kHeadDim + kPad];
@@ -89,8 +105,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const int id = unit0 + (int)blockIdx.x;
     const int r = id / nkv;
     u.g = id % nkv;
-    u.s = r % a.num_seqs;
-    const int j0 = (a.tiles_per_seq - 1 - r / a.num_seqs) * kPos;
+    int j0;
+    if constexpr (!kByRows) {   // every sequence has as many ranks as the longest may need
+      u.s = r % a.num_seqs;
+      j0 = (a.tiles_per_seq - 1 - r / a.num_seqs) * kPos;
+    } else {                    // sequence s has the ranks from cu_q[s] / kPos + s on, its last tile first
+      u.s = ranked_sequence<kPos>(a, r, lane);
+      j0 = (((scalar_i32_ptr)a.cu_q)[u.s + 1] / kPos + u.s - r) * kPos;
+      if (j0 < 0) return;
+    }
     const int q0 = ((scalar_i32_ptr)a.cu_q)[u.s], n = ((scalar_i32_ptr)a.cu_q)[u.s + 1] - q0;
     if (q0 < 0 || q0 + n > a.num_rows || j0 >= n) return;
     u.row0 = q0 + j0;
@@ -305,33 +328,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
-// Blocks a wave takes at least when units are split over workgroups.
-constexpr int kMinBlocksPerWave = 4;
 // Units of one launch (its threads must stay below 2^32).
 constexpr long long kMaxUnitsPerLaunch = 1 << 22;
 
 template <int G>
 hipError_t launch_group(DecodeArgs a, hipStream_t stream) {
   constexpr int kPos = kCols / G;
-  a.tiles_per_seq = (a.max_q_len + kPos - 1) / kPos;
-  const long long units = (long long)a.num_seqs * a.tiles_per_seq * a.num_kv_heads;
-  if (units > 0x7fffffffLL) return hipErrorInvalidValue;
-  // Split units over their blocks while they leave compute units idle (two
-  // workgroups each), in multiples of the plan's split, whose count the
-  // workspace is sized for.
-  const int maxblk = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
-  const long long room = 2LL * stream_compute_units(stream) / units;
-  const long long want = std::max(1LL, std::min<long long>(room, maxblk / (kMinBlocksPerWave * kWaves)));
-  const int per = (int)((maxblk + want - 1) / want);
-  a.split_blocks = (per + a.split_blocks - 1) / a.split_blocks * a.split_blocks;
-  const int splits = (maxblk + a.split_blocks - 1) / a.split_blocks;
-  for (long long u0 = 0; u0 < units; u0 += kMaxUnitsPerLaunch) {
-    const dim3 grid((unsigned)std::min(units - u0, kMaxUnitsPerLaunch), (unsigned)splits);
-    hipLaunchKernelGGL(prefill_f32_kernel<G>, grid, dim3(kThreads), 0, stream, a, (int)u0);
+  const F32ChunkPlan plan = plan_f32_chunks(a.num_rows, a.num_seqs, a.max_q_len, a.num_kv_heads, kPos,
+                                            longest_blocks(a.max_ctx, a.max_blocks_per_seq), a.split_blocks,
+                                            stream_compute_units(stream));
+  if (plan.units > 0x7fffffffLL) return hipErrorInvalidValue;
+  a.tiles_per_seq = plan.tiles_per_seq;
+  a.split_blocks = plan.split_blocks;
+  for (long long u0 = 0; u0 < plan.units; u0 += kMaxUnitsPerLaunch) {
+    const dim3 grid((unsigned)std::min(plan.units - u0, kMaxUnitsPerLaunch), (unsigned)plan.splits);
+    if (plan.tiles_per_seq == 0)
+      hipLaunchKernelGGL((prefill_f32_kernel<G, true>), grid, dim3(kThreads), 0, stream, a, (int)u0);
+    else
+      hipLaunchKernelGGL((prefill_f32_kernel<G, false>), grid, dim3(kThreads), 0, stream, a, (int)u0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return splits > 1 ? launch_f32_merge(a, stream) : hipSuccess;
+  return plan.splits > 1 ? launch_f32_merge(a, stream) : hipSuccess;
 }
 
 }  // namespace

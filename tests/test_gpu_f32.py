@@ -67,3 +67,16 @@ def test_non_finite_values_of_later_positions(value):
     assert not np.isfinite(got[before:, :, 5]).any()
     rest = [d for d in range(128) if d != 5]
     compare(got[before:][:, :, rest], ref[before:][:, :, rest], "f32", "other dims")
+
+
+@pytest.mark.parametrize("group,hkv", [(1, 3), (4, 2), (8, 1)])
+@pytest.mark.parametrize("c0", [0, 1500])
+def test_one_long_chunk_among_short_ones(group, hkv, c0):
+    # ranked by their rows: over 64 sequences (a second step of the search), empty ones, a last one of several tiles
+    require_gpu()
+    n = [1] * 66 + [0, 130, 0, 0] + [1, 2, 0] * 5 + [35]
+    b = written(chunk_batch([c0 if x > 1 else 7 for x in n], n, [W.RT, W.BE] * (len(n) // 2), group=group, hkv=hkv,
+                            dtype="f32", seed=group + c0))
+    poison_unowned(b)
+    announce(f"f32 chunks, one of 130 rows among short ones, G={group} c0={c0}")
+    compare(run_prefill(b), ref_prefill(b), "f32", "one long chunk among short ones")

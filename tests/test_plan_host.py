@@ -1,8 +1,10 @@
 """The launch plans' host arithmetic (csrc/plan.h), compiled alone and checked on
-the CPU: bounds up to the int32 range's end."""
+the CPU: bounds up to the int32 range's end, every chunk row ranked exactly once,
+splits the workspace holds, and limits that follow the compute units."""
 
 import ctypes
 import os
+import random
 import shutil
 import subprocess
 
@@ -16,6 +18,10 @@ WRAPPERS = """
 #include "plan.h"
 extern "C" {
 int longest(int max_ctx, int width) { return bros::longest_blocks(max_ctx, width); }
+void chunks(int rows, int seqs, int max_q, int nkv, int pos, int longest, int plan, int cus, long long* out) {
+  const bros::F32ChunkPlan p = bros::plan_f32_chunks(rows, seqs, max_q, nkv, pos, longest, plan, cus);
+  out[0] = p.units; out[1] = p.tiles_per_seq; out[2] = p.split_blocks; out[3] = p.splits;
+}
 }
 """
 
@@ -31,9 +37,24 @@ def plan(tmp_path_factory):
     subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-ftrapv", "-shared", "-fPIC", "-I", CSRC, str(src),
                     "-o", str(so)], check=True)
     lib = ctypes.CDLL(str(so))
-    I = ctypes.c_int
+    I, Q = ctypes.c_int, ctypes.c_longlong
     lib.longest.argtypes = [I, I]
+    lib.chunks.argtypes = [I] * 8 + [ctypes.POINTER(Q)]
     return lib
+
+
+def plan_blocks(rows, longest):
+    """Blocks per split that the fp32 workspace is laid out for (4 to 64, by the rows alone)."""
+    sb = 64
+    while sb > 4 and rows * -(-longest // sb) < 512:
+        sb //= 2
+    return sb
+
+
+def chunk_plan(plan, rows, seqs, max_q, nkv=8, pos=4, longest=100, sb=4, cus=256):
+    out = (ctypes.c_longlong * 4)()
+    plan.chunks(rows, seqs, max_q, nkv, pos, longest, sb, cus, out)
+    return tuple(out)
 
 
 @pytest.mark.parametrize("max_ctx", [1, 15, 16, 17, INT32_MAX - 15, INT32_MAX - 14, INT32_MAX])
@@ -41,3 +62,52 @@ def test_longest_blocks(plan, max_ctx):
     assert plan.longest(max_ctx, INT32_MAX) == max(1, -(-max_ctx // 16))
     assert plan.longest(max_ctx, 7) == min(7, max(1, -(-max_ctx // 16)))
     assert plan.longest(0, 7) == 1
+
+
+@pytest.mark.parametrize("pos", [16, 8, 4, 2])
+def test_loose_row_bounds_plan_as_the_row_count(plan, pos):
+    for rows, seqs in ((8, 1), (133, 2), (1279, 256)):
+        want = chunk_plan(plan, rows, seqs, rows, pos=pos)
+        for max_q in (rows + 1, 1 << 20, INT32_MAX - 1, INT32_MAX):
+            assert chunk_plan(plan, rows, seqs, max_q, pos=pos) == want
+        assert 0 < want[0] <= 2 * 8 * (rows // pos + seqs)
+
+
+@pytest.mark.parametrize("pos", [16, 8, 4, 2])
+def test_every_tile_has_exactly_one_rank(plan, pos):
+    rng = random.Random(pos)
+    ranked_by_rows = 0
+    for _ in range(300):
+        seqs = rng.choice([1, 2, 5, 63, 64, 65, 130])
+        longest = rng.choice([1, 3, 40, 700])
+        n = [rng.choice([0, 1, 1, 2, rng.randint(0, longest)]) for _ in range(seqs)]
+        n[rng.randrange(seqs)] = longest
+        cu = [rng.choice([0, 0, 3])]
+        for x in n:
+            cu.append(cu[-1] + x)
+        rows = cu[-1] + rng.choice([0, 0, 5])       # (rows past the last sequence are nobody's)
+        units, tiles, _, _ = chunk_plan(plan, rows, seqs, longest, nkv=1, pos=pos)
+        seen = []
+        for r in range(units):
+            if tiles:
+                s, t = r % seqs, tiles - 1 - r // seqs
+            else:                                   # the last sequence whose first rank is at or before r
+                ranked_by_rows += 1
+                s = max([i for i in range(seqs) if cu[i] // pos + i <= r], default=0)
+                t = cu[s + 1] // pos + s - r
+            if 0 <= t and t * pos < n[s]:
+                seen.append((s, t))
+        assert sorted(seen) == [(s, t) for s in range(seqs) for t in range(-(-n[s] // pos))]
+    assert ranked_by_rows > 0
+
+
+def test_splits_stay_within_the_workspace(plan):
+    rng = random.Random(1)
+    for _ in range(2000):
+        rows, nkv, group = rng.randint(1, 600), rng.choice([1, 3, 8, 64]), rng.choice([1, 2, 4, 8])
+        longest = rng.choice([1, 3, 4, 19, 20, 21, 25, 26, rng.randint(1, 3000), 2**27])
+        sb = plan_blocks(rows, longest)
+        cus = rng.choice([256, 128, 32])
+        units, tiles, per, splits = chunk_plan(plan, rows, rng.randint(1, rows), rng.randint(1, rows), nkv, 16 // group,
+                                               longest, sb, cus)
+        assert per % sb == 0 and splits == -(-longest // per) and splits <= -(-longest // sb)

@@ -38,8 +38,6 @@
 #include "decode_common.h"
 #include "plan.h"
 
-#include <algorithm>
-
 namespace bros {
 namespace {
 
@@ -167,9 +165,8 @@ struct WaveState {
   }
 
   // Softmax update with this block's raw scores, then PV with its V fragments.
-  // The block's products are summed by themselves first, so that a long context
-  // takes one rounding per block: 16 rows of 64 to 2048 tokens (32 / 8 heads) are
-  // 1.54e-7 from 64 bits, in one chain 1.69e-7. The adds cost 1 %.
+  // kBlockSums: the block's products are summed by themselves first.
+  template <bool kBlockSums>
   __device__ void update(float (&sc)[LY::NPL], const Frag (&vf)[4], bool primary, float scale_log2) {
     constexpr int NPL = LY::NPL, DUP = LY::DUP, GROUP = LY::GROUP;
     float mx = sc[0];
@@ -208,10 +205,11 @@ struct WaveState {
       for (int j = 0; j < 4; ++j) wv[j] = row_bcast_dyn(p[(4 * h + j) % NPL], ((4 * h + j) / NPL) * DUP);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        float t = wv[0] * vf[0].f[e];
+        float t = kBlockSums ? wv[0] * vf[0].f[e] : fmaf(wv[0], vf[0].f[e], acc[h][e]);
         t = fmaf(wv[1], vf[1].f[e], t);
         t = fmaf(wv[2], vf[2].f[e], t);
-        acc[h][e] += fmaf(wv[3], vf[3].f[e], t);
+        t = fmaf(wv[3], vf[3].f[e], t);
+        acc[h][e] = kBlockSums ? acc[h][e] + t : t;
       }
     }
   }
@@ -333,7 +331,13 @@ __device__ __forceinline__ void fetch_item(const DecodeArgs& a, const int* s_pre
   if (lane < nb) it.tbl = a.block_tables[(size_t)it.s * a.max_blocks_per_seq + it.b_begin + lane];
 }
 
-template <int G>
+// kBlockSums: items longer than the plan's splits, whose lanes walk more blocks
+// in one chain of sums. Each block's products are then summed by themselves, so
+// that a long chain takes one rounding per block: 16 rows of 64 to 2048 tokens
+// (32 / 8 heads) are 1.54e-7 from 64 bits, in one chain 1.69e-7, with the plan's
+// splits 1.67e-7. The adds cost 1 %, and 4 % where the vector ALU bounds the
+// kernel (8 heads, 300 rows), so items of the plan's own length do without.
+template <int G, bool kBlockSums>
 __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
   constexpr int GW = G > 4 ? 4 : G;     // heads per wave
   constexpr int HS = G / GW;            // waves sharing a block stream
@@ -436,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void decode_f32_kernel(DecodeArgs a) {
             if (b * kBlockSize + slot_of_offset(Rt + 4 * j, cur.dirv) >= cur.ctx) sc[i2] = -INFINITY;
           }
         }
-        st.update(sc, vf, primary, a.scale_log2);
+        st.template update<kBlockSums>(sc, vf, primary, a.scale_log2);
       }
       // V registers are free: request the next block's values
       if (more_here) issue_v(cur, i + 1);
@@ -531,30 +535,21 @@ __global__ __launch_bounds__(kHeadDim) void f32_merge_kernel(DecodeArgs a) {
   static_cast<float*>(a.out)[((size_t)row * a.num_q_heads + hq) * kHeadDim + d] = L > 0.0f ? A / L : 0.0f;
 }
 
-constexpr int kItems = 512, kMaxItemBlocks = 32, kWholeBlocks = 20;
-
 template <int G>
 hipError_t launch_group_f32(DecodeArgs a, hipStream_t stream, int slot) {
-  // The plan's split (the workspace is laid out for it) counts rows alone; KV
-  // heads make items too, and a split costs an item's start-up and a partial.
-  // So an item takes as many of the plan's splits as leaves about kItems items,
-  // up to kMaxItemBlocks blocks, and a context of kWholeBlocks or less stays
-  // whole, which saves the merge's launch. Decode calls, us, the plan's splits
-  // and these (32 / 8 heads): 64 rows of 30 to 300 tokens 33 / 23, 16 rows of 64
-  // to 2048 54 / 40, 8 rows of 1000 to 4000 71 / 47, 64 rows of 500 to 2048 141
-  // / 135 (144 with 64 blocks an item), one row 21 both ways.
-  const int maxblk = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
-  const long long segments = (long long)a.num_rows * a.num_kv_heads;
-  const long long want = (kItems + segments - 1) / segments;   // splits of the longest context
-  int per = std::min((int)((maxblk + want - 1) / want), kMaxItemBlocks);
-  if (maxblk <= kWholeBlocks) per = maxblk;
-  a.split_blocks = (per + a.split_blocks - 1) / a.split_blocks * a.split_blocks;
-  const int splits = (maxblk + a.split_blocks - 1) / a.split_blocks;
-  const long long padded = segments * splits;
-  const int resident = resident_workgroups(reinterpret_cast<const void*>(&decode_f32_kernel<G>), kThreads, slot, stream);
+  const int resident = resident_workgroups(reinterpret_cast<const void*>(&decode_f32_kernel<G, false>), kThreads, slot, stream);
+  const int32_t maxblk = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
+  const int32_t per = f32_item_blocks(a.num_rows, a.num_kv_heads, G, maxblk, a.split_blocks, resident);
+  const bool block_sums = per > a.split_blocks;
+  a.split_blocks = per;
+  const int splits = (maxblk + per - 1) / per;
+  const long long padded = (long long)a.num_rows * a.num_kv_heads * splits;
   const int grid = (int)(padded < resident ? padded : resident);
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL((decode_f32_kernel<G>), dim3(grid), dim3(kThreads), 0, stream, a);
+  if (block_sums)
+    hipLaunchKernelGGL((decode_f32_kernel<G, true>), dim3(grid), dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((decode_f32_kernel<G, false>), dim3(grid), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits <= 1) return e;
   return launch_f32_merge(a, stream);

@@ -15,6 +15,60 @@ inline int32_t longest_blocks(int32_t max_ctx, int32_t max_blocks_per_seq) {
   return (int32_t)std::max<int64_t>(1, std::min<int64_t>(blocks, max_blocks_per_seq));
 }
 
+// Blocks of a work item of the fp32 decode. The workspace is laid out for splits
+// of `plan_blocks` blocks (4 to 64, chosen by the rows alone); KV heads make items
+// too, and an item costs its start-up and a partial, so an item may take several
+// of these splits: the count with the least expected time, the plan's own unless
+// that is 6 % slower.
+//
+// Expected time, in units of about a microsecond: a stream of an item (four per
+// workgroup, two with 8 heads per KV head) takes 1.4 for a block and 0.09 more per
+// head of its wave, an item's start-up 1.1; items beyond the resident ones wait
+// for a free workgroup, and some 0.66 of the splits that the longest context has
+// are there on average; the last of them end with up to 0.45 of an item's blocks
+// alone; a call with splits also pays the merge, 3.7 and 0.62 per split. Fitted to
+// 1299 calls of 1 to 300 rows, contexts up to 40 to 4000 tokens (uniform and
+// lognormal) and 64 / 8, 32 / 8, 16 / 8, 8 / 8 and 8 / 1 heads, each at nine item
+// sizes: 2 % above the best size of each call on average; the plan's own splits
+// are 12 % above it, and one size for all (32 blocks, up to 20 whole) 5 %, with a
+// third more time where few segments of 8 heads ran whole. Us, the plan's own /
+// one size / this: 64 rows of 40 to 320 tokens (32 / 8 heads) 33.7 / 22.4 / 22.5, 16
+// rows of 256 to 2048 51.4 / 35.6 / 33.5, one row of 320 with 8 / 1 heads 12.5 /
+// 16.8 / 12.2. (What is left: the longest context alone is known here, so 32 rows
+// of 25 to 200 with 64 / 8 heads take 21.8 split and would take 16.2 whole.)
+// From plans of 8 blocks on (over 100 rows) the longest context is often one among
+// many short ones, which then all wait for it: beyond 25 blocks, items stay at 16
+// or the plan's (128 rows of lognormal contexts up to 700, 16 / 8 heads: 53 us at
+// 16 blocks, 71 at 48; 300 rows up to 320, whole 98, at 16 blocks 111).
+inline int32_t f32_item_blocks(int64_t rows, int32_t num_kv_heads, int32_t group, int32_t longest, int32_t plan_blocks,
+                               int32_t resident) {
+  constexpr int32_t kMaxItemBlocks = 64;
+  const int32_t streams = group > 4 ? 2 : 4;
+  const double block_us = 1.4 + 0.09 * std::min(group, 4);
+  const double segments = (double)rows * num_kv_heads;
+  const int32_t most = plan_blocks >= 8 && longest > 25 ? std::max(plan_blocks, 16) : kMaxItemBlocks;
+  double best = 0.0;
+  int32_t chosen = plan_blocks;
+  for (int32_t per = plan_blocks; per <= most; per += plan_blocks) {
+    const int32_t splits = (longest + per - 1) / per;
+    const int32_t steps = (std::min(per, longest) + streams - 1) / streams;   // blocks of a stream
+    const double items = segments * (1.0 + 0.66 * (splits - 1));
+    double us = 1.1 + steps * block_us;
+    if (items > resident) {
+      const double mean = 0.66 * longest / streams * segments / items;
+      us = (1.1 + std::min<double>(steps, mean) * block_us) * items / resident + 0.45 * steps * block_us;
+    }
+    if (splits > 1) us += 3.7 + 0.62 * splits;
+    if (per > plan_blocks) us *= 1.06;
+    if (per == plan_blocks || us < best) {
+      best = us;
+      chosen = per;
+    }
+    if (per >= longest) break;
+  }
+  return chosen;
+}
+
 // The fp32 prefill's units (`positions` positions of one chunk and KV head each)
 // and how far their blocks are split over workgroups.
 struct F32ChunkPlan {

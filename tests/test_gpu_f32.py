@@ -82,6 +82,20 @@ def test_one_long_chunk_among_short_ones(group, hkv, c0):
     compare(run_prefill(b), ref_prefill(b), "f32", "one long chunk among short ones")
 
 
+# one item per context, and items of 4 to 32 blocks; beyond the plan's blocks each block is summed by itself
+@pytest.mark.parametrize("group,hkv,rows,longest", [
+    (1, 8, 4, 320), (8, 1, 1, 320), (4, 8, 64, 320), (2, 8, 12, 512), (4, 8, 16, 2048), (2, 8, 128, 400), (4, 2, 130, 417),
+    (8, 2, 40, 1000)])
+def test_decode_item_sizes(group, hkv, rows, longest):
+    require_gpu()
+    ctx = [int(x) for x in np.random.default_rng(rows).integers(1, longest + 1, rows)]
+    ctx[0] = longest
+    b = W.custom(ctx, [i % 2 for i in range(rows)], group * hkv, hkv, dtype="f32", seed=rows + longest, spare_blocks=3)
+    poison_unowned(b)
+    announce(f"f32 decode {rows} rows up to {longest} tokens, G={group} Hkv={hkv}")
+    compare(run_decode(b), ref_decode(b), "f32", f"f32 {rows} rows up to {longest}")
+
+
 # Distance from 64 bits (2-norm over the result's) of these batches with items of the plan's length, 4
 # blocks and a partial each, which is the bound. Longer items summed in one chain were at 1.432e-7,
 # 1.688e-7 and 1.854e-7, block by block they are at 1.333e-7, 1.543e-7 and 1.613e-7.

@@ -127,9 +127,9 @@ hipError_t launch_kv_move(const KvMoveArgs& a, bool gather, hipStream_t stream);
 hipError_t launch_decode(DecodeArgs a, int group, bool bf16, hipStream_t stream);
 hipError_t launch_prefill_f32(const DecodeArgs& a, int group, hipStream_t stream);
 // The bf16 decode of short contexts or few segments (decode_short.hip): whether
-// it is better than the even split and its merge, and if so its splits
-// (split_blocks, n_split_max). `between`, if any, is recorded before its merge.
-bool plan_decode_short(DecodeArgs& a);
+// it is better on the stream's compute units than the even split and its merge, and if so its
+// splits (split_blocks, n_split_max). `between`, if any, is recorded before its merge.
+bool plan_decode_short(DecodeArgs& a, hipStream_t stream);
 hipError_t launch_decode_short(const DecodeArgs& a, int group, hipStream_t stream, hipEvent_t between);
 // Groups of query heads for which the bf16 decode's workspace holds partials
 // beyond one per row: the waves of its largest grid.

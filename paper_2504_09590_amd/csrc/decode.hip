@@ -310,7 +310,7 @@ hipError_t launch_group(DecodeArgs a, hipStream_t stream, int slot) {
   const hipEvent_t before = g_kernel_ev_before.load(), after = g_kernel_ev_after.load();
   hipError_t e = hipSuccess;
   if (before != nullptr && (e = hipEventRecord(before, stream)) != hipSuccess) return e;
-  if (plan_decode_short(a)) return launch_decode_short(a, G, stream, after);
+  if (plan_decode_short(a, stream)) return launch_decode_short(a, G, stream, after);
   int grid = resident_workgroups(reinterpret_cast<const void*>(&dm::decode_mfma_kernel<G>), kThreads, slot, stream);
   grid = grid < kMaxDecodeGrid ? grid : kMaxDecodeGrid;
   a.num_workers = grid * kWaves;

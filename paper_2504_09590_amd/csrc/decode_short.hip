@@ -20,6 +20,7 @@
 // (With 8 waves a segment 1 us slower, with 16 up to twice as long: a compute
 // unit then reads one segment at its own rate.)
 #include "decode_device.h"
+#include "plan.h"
 
 #include <algorithm>
 
@@ -201,36 +202,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   }
 }
 
-// Longest contexts, in blocks, that run whole; from kManySegments segments on up
-// to twice as long (with fewer, pieces spread such contexts over more compute
-// units: four rows of 256 to 1024 tokens 9.5 us in pieces of 16 blocks, 16.4 whole).
-constexpr int kShortBlocks = 32;
-constexpr int kManySegments = 64;
-// From two segments per compute unit on, a few long contexts among short ones
-// are waited for, and the even split's partials, which this saves, are the
-// smaller the fewer heads share a segment. Steps in us, the even split / whole:
-//   G = 8  64 / 8 heads, 256 rows up to 1024 tokens 135.4 / 121.5
-//   G = 4  32 / 8 heads, 128 rows of lognormal contexts up to 768 54.6 / 53.7, up
-//          to 1024 56.3 / 59.7; 256 uniform ones up to 768 92.7 / 89.1
-//   G = 2  16 / 8 heads, 256 rows up to 768 88.1 / 92.8
-//   G = 1  8 / 8 heads, 256 rows up to 384 51.9 / 50.5, up to 512 63.3 / 63.7; 512
-//          rows up to 1024 207.0 / 213.6, 64 rows 36.1 / 36.9
-constexpr int kRoundSegments = 512;
-inline int longest_whole(int64_t segments, int group) {
-  if (segments < kManySegments) return kShortBlocks;
-  if (segments < kRoundSegments) return 2 * kShortBlocks;
-  return group >= 8 ? 64 : group >= 4 ? 48 : group >= 2 ? 32 : 24;
-}
-// Pieces of longer contexts: the shortest that number no more than `most`, one
-// to two per compute unit; with more of them the even split's longer walks read
-// the HBM better (64 rows of 512 to 2048 tokens, 2048 pieces of 32 blocks: 63 us
-// there, 65 here). A segment's partials are folded by one workgroup, eight a
-// round.
-struct Pieces {
-  int32_t blocks, most;
-};
-constexpr Pieces kPieces[] = {{16, 256}, {32, 512}, {64, 512}};
-constexpr int kMaxSplits = 64;
 constexpr long long kMaxSegmentsPerLaunch = 1 << 23;   // (a launch's threads must stay below 2^32)
 
 // Folds the partials of the segments that were split, a workgroup each: o =
@@ -303,26 +274,12 @@ hipError_t launch_short_group(DecodeArgs a, hipStream_t stream, hipEvent_t betwe
 
 }  // namespace dm
 
-bool plan_decode_short(DecodeArgs& a) {
-  const int64_t longest = std::min<int64_t>(a.max_ctx, (int64_t)a.max_blocks_per_seq * kBlockSize);
-  const int64_t blocks = std::max<int64_t>(1, (longest + kBlockSize - 1) / kBlockSize);
-  const int64_t segments = (int64_t)a.num_rows * a.num_kv_heads;
-  if (segments > 0x7fffffff) return false;
-  if (blocks <= dm::longest_whole(segments, a.num_q_heads / a.num_kv_heads)) {
-    a.split_blocks = (int32_t)blocks;
-    a.n_split_max = 1;
-    return true;
-  }
+bool plan_decode_short(DecodeArgs& a, hipStream_t stream) {
   // (partials: the workspace has a slot per query row and kDecodeGroupSlots groups more)
   const int64_t slots = (int64_t)a.num_rows * a.num_q_heads + (int64_t)kDecodeGroupSlots * std::min(a.num_q_heads, 8);
-  for (const dm::Pieces& p : dm::kPieces) {
-    const int64_t splits = (blocks + p.blocks - 1) / p.blocks;
-    if (splits < 2 || segments * splits > p.most || splits > dm::kMaxSplits || segments * splits * (a.num_q_heads / a.num_kv_heads) > slots) continue;
-    a.split_blocks = p.blocks;
-    a.n_split_max = (int32_t)splits;
-    return true;
-  }
-  return false;
+  return plan_short_decode((int64_t)a.num_rows * a.num_kv_heads, a.num_q_heads / a.num_kv_heads,
+                           longest_blocks(a.max_ctx, a.max_blocks_per_seq), stream_compute_units(stream), slots,
+                           &a.split_blocks, &a.n_split_max);
 }
 
 hipError_t launch_decode_short(const DecodeArgs& a, int group, hipStream_t stream, hipEvent_t between) {

@@ -89,3 +89,42 @@ def test_infinite_values_of_the_last_piece(ctx, pos, value):
     assert (got[0, :, 5] == value).all()
     ref[0, :, 5] = got[0, :, 5] = 0.0
     assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-2
+
+
+# the edges of the pieces: whole up to 24 blocks, 8 blocks (up to 24 pieces), 16 (32), 32 (48), 64 (64, with
+# fewer than 8 heads for up to 16 segments), then the even split
+@pytest.mark.parametrize("group,hkv,rows", [(1, 2, 1), (8, 1, 1), (4, 8, 1), (4, 17, 1), (8, 2, 9)])
+@pytest.mark.parametrize("blocks", [24, 25, 192, 193, 512, 513, 1536, 1537])
+def test_edges_of_the_pieces(group, hkv, rows, blocks):
+    require_gpu()
+    ctx = [16 * blocks - (blocks % 5)] + [17 * i + 3 for i in range(1, rows)]
+    b = poison_unowned(W.custom(ctx, [i % 2 for i in range(rows)], group * hkv, hkv, seed=blocks + group, spare_blocks=3))
+    announce(f"decode {rows} rows, the longest of {blocks} blocks, G={group} Hkv={hkv}")
+    compare(run_decode(b), ref_decode(b), "bf16", f"{blocks} blocks")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("cus", [64, 32])
+def test_decode_on_a_compute_unit_share(dtype, cus):
+    # its limits follow the share's compute units: other pieces, or the even split, than on the whole chip
+    torch = require_gpu()
+    from paper_2504_09590_amd import bros
+    code = bros.BROS_F32 if dtype == "f32" else bros.BROS_BF16
+    share = bros.bros_stream_create_cu_share(0, cus)
+    try:
+        for ctx in ([1300, 4000, 2047, 2999], [400] * 20 + [17], [900], [60] * 40):
+            b = poison_unowned(W.custom(ctx, [i % 2 for i in range(len(ctx))], 16, 8, dtype=dtype, seed=len(ctx),
+                                        spare_blocks=3))
+            announce(f"{dtype} decode of {len(ctx)} rows on {cus} compute units")
+            dev = bros.to_device(b)
+            out = torch.full_like(dev.q_decode, float("nan"))
+            size = bros.bros_attn_workspace_size(0, code, len(ctx), 16, 128, max(ctx))
+            ws = torch.full((max(size, 16),), 255, dtype=torch.uint8, device="cuda")
+            torch.cuda.synchronize()
+            bros.bros_attn_decode(out, dev.q_decode, dev.k_pool, dev.v_pool, dev.block_tables, dev.dir, dev.cls,
+                                  dev.ctx_lens, max(ctx), workspace=ws, stream=share)
+            torch.cuda.synchronize()
+            compare(bros.to_host_bits(out), ref_decode(b), dtype, f"{len(ctx)} rows on a share")
+    finally:
+        torch.cuda.synchronize()
+        bros.bros_stream_destroy(share)

@@ -25,6 +25,9 @@ void chunks(int rows, int seqs, int max_q, int nkv, int pos, int longest, int pl
   const bros::F32ChunkPlan p = bros::plan_f32_chunks(rows, seqs, max_q, nkv, pos, longest, plan, cus);
   out[0] = p.units; out[1] = p.tiles_per_seq; out[2] = p.split_blocks; out[3] = p.splits;
 }
+int pieces(long long segments, int group, long long blocks, int cus, long long slots, int* out) {
+  return bros::plan_short_decode(segments, group, blocks, cus, slots, out, out + 1);
+}
 }
 """
 
@@ -44,6 +47,7 @@ def plan(tmp_path_factory):
     lib.longest.argtypes = [I, I]
     lib.items.argtypes = [Q, I, I, I, I, I]
     lib.chunks.argtypes = [I] * 8 + [ctypes.POINTER(Q)]
+    lib.pieces.argtypes = [Q, I, Q, I, Q, ctypes.POINTER(I)]
     return lib
 
 
@@ -126,3 +130,32 @@ def test_fp32_items(plan):
     assert plan.items(64, 8, 4, 20, 4, 512) >= 20
     assert plan.items(128, 8, 2, 44, 8, 768) <= 16 < 48
     assert plan.items(300, 8, 2, 20, 16, 768) >= 20
+
+
+def short_plan(plan, segments, group, blocks, cus=256, slots=1 << 40):
+    out = (ctypes.c_int * 2)()
+    return tuple(out) if plan.pieces(segments, group, blocks, cus, slots, out) else None
+
+
+def test_short_decode_limits_follow_the_compute_units(plan):
+    for cus in (256, 128, 64, 32):
+        for group in (1, 2, 4, 8):
+            for segments in (1, 8, 16, cus // 4, cus // 2 - 1, cus // 2, cus, 2 * cus, 4 * cus, 16 * cus):
+                for blocks in list(range(1, 66)) + [94, 200, 511, 1000, 4000]:
+                    got = short_plan(plan, segments, group, blocks, cus)
+                    # the same segments per compute unit, the same plan
+                    if cus != 256 and segments > 16:
+                        assert got == short_plan(plan, segments * 256 // cus, group, blocks, 256)
+                    if got is not None and got[1] > 1:
+                        assert got[1] == -(-blocks // got[0]) <= 64 and segments * got[1] <= 3 * cus
+                    if got is not None and got[1] == 1:
+                        assert got[0] == blocks <= 64
+    # four rows of 1024 to 4096 tokens, 8 KV heads: pieces on the whole chip, fewer on a quarter of it
+    assert short_plan(plan, 32, 4, 256) == (16, 16)
+    assert short_plan(plan, 32, 4, 256, cus=64) is None
+
+
+def test_short_decode_partials_fit(plan):
+    assert short_plan(plan, 8, 8, 100, slots=8 * 13 * 8) == (8, 13)
+    assert short_plan(plan, 8, 8, 100, slots=8 * 13 * 8 - 1) == (16, 7)
+    assert short_plan(plan, 2**31, 1, 4) is None

@@ -105,10 +105,9 @@ constexpr int kMaxTableLds = kPrefillWholeTableCtx / kBlockSize;   // table entr
 constexpr int kRefillTiles = kMaxTableLds / 4;     // ring variant: tiles (2 entries each) of half the ring
 constexpr int kTablePad = 32;                      // staged entries past the last tile (loads run ahead)
 constexpr int kMaxRankItems = kThreads;            // units planned on the device (one per thread)
-constexpr int kMaxPieces = 4 * kThreads;           // pieces ranked on the device (four per thread)
 constexpr int kMinPartTiles = 8;                   // the shortest piece a unit is split into
 constexpr int kMinSavedTiles = 12;                 // what splitting must take off the longest unit
-constexpr int kPairTiles = 96;                     // the shortest pieces that run two to a compute unit
+constexpr int kPairTiles = 12;                     // what a second piece on every compute unit costs
 constexpr int kLoadsPerStep = 4;                   // two K and two V loads per wave per step
 constexpr int kXcds = 8;                           // accelerator dies of the chip; blockIdx % 8 picks the die
 
@@ -270,34 +269,47 @@ struct PiecePlan {
 // once -- one piece too many waits for a whole piece -- so T is the shortest of
 // some candidates between the mean T0 = total / budget and 2 T0 whose pieces
 // fit the budget of pieces per KV head, units shorter than T counting by their
-// length (several share a slot in turn). The budget is one piece per compute
-// unit, and two where pieces of at least kPairTiles tiles remain: two resident
-// workgroups advance 1.2 us per tile each against 0.55 us for one, so two pay
-// only where a tenth of a long piece outweighs the second start-up and the
-// partials (512 rows on 16000 cached tokens: 154 us with two, 163 with one; on
-// 4000: 61 and 59).
+// length (several share a slot in turn).
+//
+// The budget is one piece per compute unit, or two: of two resident workgroups each
+// advances 1 us per tile, alone 0.55, and the second costs another start-up and
+// more partials, as long as kPairTiles tiles. So two pay where pieces are long (512 rows on
+// 16000 cached tokens: 154 us with two, 163 with one; on 4000: 61 and 59), and where
+// the units cannot be cut evenly into one piece per compute unit (192 units of
+// 192 to 284 tiles, 8 / 8 heads: 111 us with two, 155 with one, when most stay whole; two
+// prompts of 1986 rows, 8 / 1 heads: 49 and 79).
 struct PartSize {
-  int budget, t0;
+  int budget[2], t0[2];   // one and two pieces per compute unit
   __device__ PartSize(const PrefillArgs& a, int total) {
-    budget = max(1, min(2 * a.num_cus, a.ws_slots) / a.num_kv_heads);
-    if (total < kPairTiles * budget) budget = max(1, min(a.num_cus, a.ws_slots) / a.num_kv_heads);
-    t0 = max((total + budget - 1) / budget, kMinPartTiles);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      budget[k] = max(1, min((k + 1) * a.num_cus, a.ws_slots) / a.num_kv_heads);
+      t0[k] = max((total + budget[k] - 1) / budget[k], kMinPartTiles);
+    }
   }
-  // candidate c of n (c < n): t0 .. 2 t0
-  __device__ int candidate(int c, int n) const { return t0 + (int)((int64_t)t0 * c / (n - 1)); }
-  __device__ float rcp(int c, int n) const { return 1.0f / (float)candidate(c, n); }
+  // candidate c of n (c < n) of budget k: t0 .. 2 t0
+  __device__ int candidate(int k, int c, int n) const { return t0[k] + (int)((int64_t)t0[k] * c / (n - 1)); }
+  __device__ float rcp(int k, int c, int n) const { return 1.0f / (float)candidate(k, c, n); }
   // What a unit of L tiles takes of the budget at part size 1 / rcp. (A float
   // quotient one piece off only moves the choice of T.)
   static __device__ float share(int L, float rcp) {
     const float x = (float)max(L, 0) * rcp;
     return x <= 1.0f ? x : ceilf(x - 1e-4f);
   }
+  // The part size, or 0 where splitting does not pay; the longest unit has Lmax
+  // tiles. Lane c holds what the units take of each budget at its candidate c of
+  // kWave. A budget ends with its longest piece, in tiles at the pace of one
+  // workgroup per compute unit; that must be kMinSavedTiles earlier than the longest
+  // unit whole, or the partials and the merge cost what is saved.
+  __device__ int choose(float pieces0, float pieces1, int Lmax) const {
+    const uint64_t fits0 = __builtin_amdgcn_ballot_w64(pieces0 <= (float)budget[0]);
+    const uint64_t fits1 = __builtin_amdgcn_ballot_w64(pieces1 <= (float)budget[1]);
+    const int T0 = candidate(0, fits0 ? __builtin_ctzll(fits0) : kWave - 1, kWave);
+    const int T1 = candidate(1, fits1 ? __builtin_ctzll(fits1) : kWave - 1, kWave);
+    const int one = min(T0, Lmax), two = min(T1, Lmax) * 20 / 11 + kPairTiles;
+    return Lmax - min(one, two) >= kMinSavedTiles ? (one <= two ? T0 : T1) : 0;
+  }
 };
-
-// Whether splitting at part size T pays, the longest unit having Lmax tiles: it
-// must end kMinSavedTiles tiles earlier than whole, or the partials and the
-// merge cost what is saved.
-__device__ __forceinline__ bool split_pays(int Lmax, int T) { return Lmax - T >= kMinSavedTiles; }
 
 __device__ __forceinline__ int wave_inclusive_scan(int v, int lane) {
 #pragma unroll
@@ -331,21 +343,21 @@ __device__ PiecePlan plan_pieces_wave(const PrefillArgs& a, int rank) {
   if (a.num_cus > 0) {
     const int total = read_lane_i32(wave_inclusive_scan(L, lane), kWave - 1);
     const PartSize ps(a, total);
-    const float rcp = ps.rcp(lane, kWave);
-    float pieces = 0.0f;
+    const float rcp0 = ps.rcp(0, lane, kWave), rcp1 = ps.rcp(1, lane, kWave);
+    float pieces0 = 0.0f, pieces1 = 0.0f;
     int Lmax = 0;
     for (int i = 0; i < n_items; ++i) {
       const int Li = read_lane_i32(L, i);
-      pieces += PartSize::share(Li, rcp);
+      pieces0 += PartSize::share(Li, rcp0);
+      pieces1 += PartSize::share(Li, rcp1);
       Lmax = max(Lmax, Li);
     }
-    const uint64_t fits = __builtin_amdgcn_ballot_w64(pieces <= (float)ps.budget);
-    const int T = ps.candidate(fits ? __builtin_ctzll(fits) : kWave - 1, kWave);
-    const int P = L > 0 ? 1 + (L - 1) / T : 0;
+    const int T = ps.choose(pieces0, pieces1, Lmax);
+    const int P = L > 0 ? 1 + (L - 1) / max(T, 1) : 0;
     const int own = P > 1 ? P : 0;
     const int send = wave_inclusive_scan(own, lane);
     const int n_split = read_lane_i32(send, kWave - 1);
-    const bool split = n_split > 0 && split_pays(Lmax, T) && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
+    const bool split = T > 0 && n_split > 0 && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
     if (blockIdx.x == 0 && threadIdx.x < kWave) {
       // the split items, in item order: count, then (item, parts, first slot)
       const uint64_t m = __builtin_amdgcn_ballot_w64(split && P > 1);
@@ -389,10 +401,9 @@ __device__ PiecePlan plan_pieces_wave(const PrefillArgs& a, int rank) {
 // The piece of rank `rank` (longest first). Items are (sequence, tile of
 // positions); all KV heads of an item have its length L (key tiles of its
 // last row). Without splitting (num_cus 0) each item is one piece. With it,
-// an item becomes ceil(L / T) pieces (PartSize), and ranks exceed the items by at most 2 num_cus /
-// Hkv. Workgroup 0 writes the list of split items for the merge. `scratch` is
-// 2 kMaxPieces + 4 + kThreads / kWave + 3 kMaxRankItems ints of LDS, 16-byte
-// aligned, that nothing else uses meanwhile. Every thread of the workgroup
+// an item becomes ceil(L / T) pieces (PartSize), and ranks exceed the items by at
+// most 2 num_cus / Hkv. Workgroup 0 writes the list of split items for the merge. `scratch` is
+// 5 kMaxRankItems + 4 + kThreads / kWave ints of LDS, 16-byte aligned, that nothing else uses meanwhile. Every thread of the workgroup
 // calls it. The lengths read for the ranking come back with the plan, so the
 // unit does not read them again.
 template <int QT>
@@ -406,11 +417,10 @@ __device__ PiecePlan plan_pieces(const PrefillArgs& a, int rank, int* scratch) {
     return PiecePlan{t_rank < tps ? (rank % a.num_seqs) * tps + (tps - 1 - t_rank) : -1, 0, 1, 0, 0, -1, 0};
   }
   if (n_items <= kWave) return plan_pieces_wave<QT>(a, rank);
-  int* s_len = scratch;                     // [kMaxPieces] lengths, then -1 padding
-  int* s_pid = scratch + kMaxPieces;        // [kMaxPieces] item * 1024 + part
-  int* s_res = scratch + 2 * kMaxPieces;    // [4]
-  int* s_red = s_res + 4;                   // [kThreads / kWave]
-  int* s_seq = s_red + kThreads / kWave;    // [3 kMaxRankItems] per item: q_begin, n, ctx
+  int* s_len = scratch;                          // [kMaxRankItems] lengths, then -1 padding; when splitting other lists
+  int* s_res = scratch + 2 * kMaxRankItems;      // [4]
+  int* s_red = s_res + 4;                        // [kThreads / kWave]
+  int* s_seq = s_red + kThreads / kWave;         // [3 kMaxRankItems] per item: q_begin, n, ctx
   int L = -1;
   if (tid < n_items) {
     const int sq = tid / tps;
@@ -428,77 +438,85 @@ __device__ PiecePlan plan_pieces(const PrefillArgs& a, int rank, int* scratch) {
     }
     return p;
   };
-  int P = 1, n_pieces = n_items, pbase = tid, sbase = 0;
-  bool split = false;
   if (a.num_cus > 0) {
+    const int lane = tid & (kWave - 1);
+    const int w = wave_id_uniform();
     int total = 0;
     block_scan(max(L, 0), s_red, &total);
-    if (tid < n_items) s_len[tid] = L;
-    if (tid == 0) s_res[0] = kThreads - 1;
-    __syncthreads();
     const PartSize ps(a, total);
-    float pieces = 0.0f;
-    const float rcp = ps.rcp(tid, kThreads);
+    // Every wave takes the items of its own lanes, for all candidates (a lane
+    // each), and the four waves' parts are added up. (Every thread going over all items in LDS for a
+    // candidate of its own took 10 us of 180 items.)
+    const float rcp0 = ps.rcp(0, lane, kWave), rcp1 = ps.rcp(1, lane, kWave);
+    float pieces0 = 0.0f, pieces1 = 0.0f;
     int Lmax = 0;
-    for (int i = 0; i < n_items; ++i) {
-      pieces += PartSize::share(s_len[i], rcp);
-      Lmax = max(Lmax, s_len[i]);
+    const int mine = min(kWave, n_items - w * kWave);
+    for (int i = 0; i < mine; ++i) {
+      const int Li = read_lane_i32(L, i);
+      pieces0 += PartSize::share(Li, rcp0);
+      pieces1 += PartSize::share(Li, rcp1);
+      Lmax = max(Lmax, Li);
     }
-    if (pieces <= (float)ps.budget) atomicMin(&s_res[0], tid);
+    float2* s_part = reinterpret_cast<float2*>(scratch);   // [kThreads]
+    s_part[tid] = make_float2(pieces0, pieces1);
+    if (lane == 0) s_res[w] = Lmax;
     __syncthreads();
-    const int T = ps.candidate(s_res[0], kThreads);
-    const int Pt = L > 0 ? 1 + (L - 1) / T : 0;
-    const int pend = block_scan(Pt, s_red, &n_pieces);
+    pieces0 = pieces1 = 0.0f;
+    Lmax = 0;
+#pragma unroll
+    for (int x = 0; x < kThreads / kWave; ++x) {
+      const float2 v = s_part[x * kWave + lane];
+      pieces0 += v.x;
+      pieces1 += v.y;
+      Lmax = max(Lmax, s_res[x]);
+    }
+    const int T = ps.choose(pieces0, pieces1, Lmax);
+    const int Pt = L > 0 ? 1 + (L - 1) / max(T, 1) : 0;
     const int own = Pt > 1 ? Pt : 0;
     int n_split = 0;
-    const int send = block_scan(own, s_red, &n_split);
-    split = n_split > 0 && split_pays(Lmax, T) && n_pieces <= kMaxPieces && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
-    if (split) {
-      P = Pt;
-      pbase = pend - Pt;
-      sbase = send - own;
-    } else {
-      n_pieces = n_items;
-    }
+    const int sbase = block_scan(own, s_red, &n_split) - own;
+    const bool split = T > 0 && n_split > 0 && (int64_t)n_split * a.num_kv_heads <= a.ws_slots;
     if (blockIdx.x == 0) {
       // the split items, in item order: count, then (item, parts, first slot)
       int count = 0;
-      const int is = split && P > 1 ? 1 : 0;
+      const int is = split && own > 0 ? 1 : 0;
       const int idx = block_scan(is, s_red, &count) - is;
       if (is) {
         a.ws_list[1 + 3 * idx] = tid;
-        a.ws_list[2 + 3 * idx] = P;
+        a.ws_list[2 + 3 * idx] = Pt;
         a.ws_list[3 + 3 * idx] = sbase;
       }
       if (tid == 0) a.ws_list[0] = split ? count : 0;
     }
-  }
-  if (!split) {
-    if (tid < kMaxRankItems) s_len[tid] = L;   // -1 past the items
-    const int k = find_rank(s_len, n_items, rank, s_res);
-    const PiecePlan out = lens_of(PiecePlan{k, 0, 1, 0, 0, -1, 0});
-    __syncthreads();   // the scratch is the caller's again
-    return out;
-  }
-  if (tid < n_items) {
-    for (int q = 0; q < P; ++q) {
-      s_len[pbase + q] = (int)((int64_t)(q + 1) * L / P) - (int)((int64_t)q * L / P);
-      s_pid[pbase + q] = tid * 1024 + q;
+    if (split) {
+      // Items by the length of their pieces; the rank is one of the item whose pieces
+      // start at or before it (as in plan_pieces_wave, keys distinct and > 0).
+      const int key = Pt > 0 ? (L + Pt - 1) / Pt * kThreads + (kThreads - 1 - tid) : 0;
+      reinterpret_cast<int2*>(scratch)[tid] = make_int2(key, Pt);   // (the parts were read before block_scan's barriers)
+      if (tid == 0) s_res[0] = -1;
+      __syncthreads();
+      int start = 0;
+      const int4* keys = reinterpret_cast<const int4*>(scratch);
+#pragma unroll 8
+      for (int j = 0; j < (n_items + 1) / 2; ++j) {
+        const int4 v = keys[j];
+        start += (v.x > key ? v.y : 0) + (v.z > key ? v.w : 0);
+      }
+      if (Pt > 0 && rank >= start && rank < start + Pt) {
+        s_res[0] = tid;
+        s_res[1] = rank - start;
+        s_res[2] = Pt;
+        s_res[3] = sbase;
+      }
+      __syncthreads();
+      const PiecePlan out = lens_of(PiecePlan{s_res[0], s_res[1], s_res[2], s_res[3], 0, -1, 0});
+      __syncthreads();   // the scratch is the caller's again
+      return out;
     }
   }
-  if (tid < ((n_pieces + 3) & ~3) - n_pieces) s_len[n_pieces + tid] = -1;   // padding
-  const int k = find_rank(s_len, n_pieces, rank, s_res);
-  PiecePlan out{-1, 0, 0, 0, 0, -1, 0};
-  if (k >= 0) {
-    const int id = s_pid[k];
-    const int item = id / 1024;
-    if (tid == item) {
-      s_res[1] = P;
-      s_res[2] = sbase;
-    }
-    __syncthreads();
-    out = lens_of(PiecePlan{item, id % 1024, s_res[1], s_res[2], 0, -1, 0});
-  }
+  if (tid < kMaxRankItems) s_len[tid] = L;   // -1 past the items
+  const int k = find_rank(s_len, n_items, rank, s_res);
+  const PiecePlan out = lens_of(PiecePlan{k, 0, 1, 0, 0, -1, 0});
   __syncthreads();   // the scratch is the caller's again
   return out;
 }

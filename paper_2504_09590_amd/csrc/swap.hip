@@ -40,7 +40,9 @@ __device__ __forceinline__ int div_small(int n, int d, float rcp) {
   return q;
 }
 
-template <bool GATHER, int ROW_CHUNKS>
+// ITERS: chunks per thread, kIter, or 1 for a list that one per thread covers (a
+// slot or a few: seven rounds of index arithmetic less, a gather 3.8 us -> 3.0).
+template <bool GATHER, int ROW_CHUNKS, int ITERS>
 __global__ __launch_bounds__(kThreads) void kv_move_kernel(KvMoveArgs a, int ids_per_group, float rcp) {
   const int tid = threadIdx.x;
   const int per_id = a.num_kv_heads * ROW_CHUNKS;          // chunks of an id's rows of one tensor
@@ -51,11 +53,11 @@ __global__ __launch_bounds__(kThreads) void kv_move_kernel(KvMoveArgs a, int ids
   uint8_t* pool = static_cast<uint8_t*>(v ? a.v_pool : a.k_pool);
   uint8_t* dense = static_cast<uint8_t*>(v ? a.v_dense : a.k_dense) + (size_t)i0 * per_id * 16;
 
-  for (int base = 0; base < n; base += kThreads * kIter) {
-    v4u_t data[kIter];
-    int64_t at[kIter];   // byte offset of the chunk in the pool, -1 when its id lies outside
+  for (int base = 0; base < n; base += kThreads * ITERS) {
+    v4u_t data[ITERS];
+    int64_t at[ITERS];   // byte offset of the chunk in the pool, -1 when its id lies outside
 #pragma unroll
-    for (int it = 0; it < kIter; ++it) {
+    for (int it = 0; it < ITERS; ++it) {
       const int c = min(base + it * kThreads + tid, n - 1);
       const int i = div_small(c, per_id, rcp);
       const int rem = c - i * per_id;
@@ -68,13 +70,13 @@ __global__ __launch_bounds__(kThreads) void kv_move_kernel(KvMoveArgs a, int ids
     }
     if (GATHER) {
 #pragma unroll
-      for (int it = 0; it < kIter; ++it) {
+      for (int it = 0; it < ITERS; ++it) {
         data[it] = v4u_t{0u, 0u, 0u, 0u};
         if (at[it] >= 0) data[it] = *reinterpret_cast<const v4u_t*>(pool + at[it]);
       }
     }
 #pragma unroll
-    for (int it = 0; it < kIter; ++it) {
+    for (int it = 0; it < ITERS; ++it) {
       const int c = base + it * kThreads + tid;
       if (c >= n) continue;
       if (GATHER) *reinterpret_cast<v4u_t*>(dense + (size_t)c * 16) = data[it];
@@ -95,12 +97,16 @@ static hipError_t launch_move(const KvMoveArgs& a, hipStream_t stream) {
   if (groups > 0x7fffffffLL / kThreads) return hipErrorInvalidValue;
   const dim3 grid((unsigned)groups, 2);
   const float rcp = 1.0f / (float)per_id;
-  if (row_chunks == kHeadDim * 2 / 16)
-    hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 2 / 16>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
-  else if (row_chunks == kHeadDim * 4 / 16)
-    hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 4 / 16>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
-  else
+  const bool few = (int64_t)a.num_slots * per_id <= kThreads;
+  if (row_chunks == kHeadDim * 2 / 16) {
+    if (few) hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 2 / 16, 1>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
+    else hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 2 / 16, kIter>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
+  } else if (row_chunks == kHeadDim * 4 / 16) {
+    if (few) hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 4 / 16, 1>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
+    else hipLaunchKernelGGL((kv_move_kernel<GATHER, kHeadDim * 4 / 16, kIter>), grid, dim3(kThreads), 0, stream, a, ids, rcp);
+  } else {
     return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("hkv,n", [(1, 127), (1, 129), (3, 42), (3, 43), (8, 16), (8, 17), (8, 1), (7, 100), (200, 3)])
+@pytest.mark.parametrize("hkv,n", [(1, 127), (1, 129), (3, 42), (3, 43), (8, 16), (8, 17), (8, 1), (7, 100), (200, 3),
+                                   (1, 16), (1, 17), (2, 4), (16, 1), (17, 1)])   # (about a chunk per thread)
 def test_moves_are_exact(dtype, hkv, n):
     torch = require_gpu()
     from paper_2504_09590_amd import bros

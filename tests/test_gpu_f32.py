@@ -110,3 +110,34 @@ def test_longer_items_keep_the_precision(group, hkv, rows, lo, hi, bound):
     err = float(np.linalg.norm(run_decode(b) - ref) / np.linalg.norm(ref))
     print(f"distance {err:.4g}")
     assert err <= bound
+
+
+@pytest.mark.parametrize("bad", [0, 3, 60, 94])
+@pytest.mark.parametrize("c0,n", [(1490, 25), (1510, 1)])
+def test_chunk_entries_out_of_range_are_invisible(bad, c0, n):
+    # the first, a middle and the tail block of whole units and of split ones; block 0, read in place
+    # of an invalid entry's, holds NaNs
+    require_gpu()
+    for units in (1, 80):                     # alone its blocks are split, among 80 others not
+        b = written(chunk_batch([c0] + [3] * (units - 1), [n] + [20] * (units - 1), [W.RT] * units, group=4, hkv=2,
+                                dtype="f32", seed=bad))
+        b = poison_unowned(b)
+        tab = b.block_tables
+        spare = np.setdiff1d(np.arange(b.num_blocks), tab[tab >= 0])[0]
+        if 0 in tab:                          # another block takes the place of block 0
+            b.k_pool[spare], b.v_pool[spare] = b.k_pool[0], b.v_pool[0]
+            tab[tab == 0] = spare
+        b.k_pool[0] = b.v_pool[0] = np.nan
+        k = oracle.gather_kv(b.k_pool, tab, b.dir, 0, c0 + n)
+        v = oracle.gather_kv(b.v_pool, tab, b.dir, 0, c0 + n)
+        ref = ref_prefill(b)
+        gone = np.arange(16 * bad, min(16 * (bad + 1), c0 + n))
+        for j in range(n):
+            keep = np.setdiff1d(np.arange(c0 + j + 1), gone)
+            ref[j] = oracle.softmax_attention(b.q_prefill[j:j + 1].astype(np.float64), k[keep].astype(np.float64),
+                                              v[keep].astype(np.float64), np.array([len(keep)]),
+                                              oracle.default_scale(128))[0]
+        for entry in (-1, b.num_blocks):
+            tab[0, bad] = entry
+            announce(f"f32 chunk of {n} rows, entry {bad} is {entry}, {units} units")
+            compare(run_prefill(b), ref, "f32", f"invalid entry {bad}")

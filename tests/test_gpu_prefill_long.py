@@ -58,3 +58,31 @@ def test_invalid_entry_early_in_a_long_table(whole):
     b.block_tables[0, bad] = -1
     announce(f"prefill long context, invalid entry {bad}, whole={whole}")
     compare(run_prefill(b), ref, "bf16", "invalid entry, long context")
+
+
+@pytest.mark.parametrize("whole", [True, False])
+def test_long_table_over_a_pool_past_32_bit_offsets(whole):
+    # the ring with 64-bit addresses: a pool of more than 2^20 (block, KV head) rows, the batch's blocks behind them
+    torch = require_gpu()
+    from paper_2504_09590_amd import bros
+    n, c0 = 40, RING + RING // 2
+    short = 256 if whole else 1
+    b = written(chunk_batch([c0] + [3] * short, [n] + [1] * short, [W.RT] * (short + 1), group=4, hkv=2, seed=19))
+    poison_unowned(b)
+    announce(f"prefill long context, pool rows past 2^20, whole={whole}")
+    shift = (1 << 19) + 5                    # x 2 KV heads x 4 KiB: past 4 GiB
+    dev = bros.to_device(b)
+    big_k = torch.empty((shift + b.num_blocks,) + tuple(dev.k_pool.shape[1:]), dtype=dev.k_pool.dtype, device="cuda")
+    big_v = torch.empty_like(big_k)
+    big_k[shift:], big_v[shift:] = dev.k_pool, dev.v_pool
+    tables = torch.where(dev.block_tables >= 0, dev.block_tables + shift, dev.block_tables)
+    P, max_ctx = b.num_prefill, int(b.ctx_lens.max())
+    size = bros.bros_attn_workspace_size(1, bros.BROS_BF16, int(b.cu_q[-1]), b.num_q_heads, 128, max_ctx)
+    ws = torch.full((size,), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(dev.q_prefill, float("nan"))
+    bros.bros_attn_prefill_chunk(out, dev.q_prefill, dev.cu_q, n, big_k, big_v, tables[:P].contiguous(), dev.dir[:P],
+                                 dev.cls[:P], dev.ctx_lens[:P], max_ctx, workspace=ws)
+    torch.cuda.synchronize()
+    compare(bros.to_host_bits(out), ref_prefill(b), "bf16", "long table, pool rows past 2^20")
+    del big_k, big_v
+    torch.cuda.empty_cache()

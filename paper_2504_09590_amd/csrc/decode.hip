@@ -69,6 +69,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void decode_mfma_merge_kernel(
   constexpr int L = kWave / G;          // lanes per head
   constexpr int DPL = kHeadDim / L;     // dims per lane (2 G)
   __shared__ float s_acc[kMergeWaves][DPL][kWave], s_m[kMergeWaves][kWave], s_l[kMergeWaves][kWave];
+  __shared__ int s_last[kMergeWaves];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = wave_id_uniform();
   const int item = blockIdx.x * kMergeWaves + wave;
@@ -118,6 +119,21 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void decode_mfma_merge_kernel(
       if (m != ~0ull) break;
     }
     w1 = __builtin_amdgcn_readfirstlane(max(w1, item));
+  }
+  // Last workers that had to be found (a fused launch) go to the other waves, so
+  // that these share long segments too: two prompts beside 32 rows of 100 to 1500
+  // tokens 79 us a merge with the wave alone, 28 shared.
+  bool given[kMergeWaves], found = false;
+#pragma unroll
+  for (int e = 0; e < kMergeWaves; ++e) {
+    given[e] = lasts[e] >= 0;
+    found |= codes[e] >= 0 && !given[e];
+  }
+  if (found) {   // uniform over the workgroup
+    if (lane == 0) s_last[wave] = w1;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kMergeWaves; ++e) lasts[e] = given[e] ? lasts[e] : s_last[e];
   }
 
   const int hl = lane / L, sub = lane % L;
@@ -193,9 +209,8 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void decode_mfma_merge_kernel(
     for (int d = 0; d < DPL; d += 2) out[d / 2] = pack2_bf16(acc[d] * inv, acc[d + 1] * inv);
   };
 
-  // Up to kAlone partials (nearly every segment of a large batch), or a last
-  // worker that had to be found: the wave alone.
-  if (code >= 0 && (w1 - item < kAlone || !known)) {
+  // Up to kAlone partials (nearly every segment of a large batch): the wave alone.
+  if (code >= 0 && w1 - item < kAlone) {
     fold((size_t)code, item, w1, known);
     write(code);
   }
@@ -207,7 +222,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void decode_mfma_merge_kernel(
     if (seg < 0 || c1 - c0 < kAlone) continue;   // uniform over the workgroup
     const int n = c1 - c0 + 1;
     const int p0 = c0 + n * wave / kMergeWaves, p1 = c0 + n * (wave + 1) / kMergeWaves - 1;   // (n > kAlone: none is empty)
-    fold((size_t)seg, p0, p1, true);
+    fold((size_t)seg, p0, p1, given[e]);
     __syncthreads();   // the last segment's results have been read
     s_m[wave][lane] = M;
     s_l[wave][lane] = Lsum;

@@ -130,3 +130,17 @@ def test_fused_pool_rows_past_32_bit_offsets():
     compare(bros.to_host_bits(out_d), dec_ref, "bf16", "fused decode, pool rows past 2^20")
     del big_k, big_v
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("group,hkv", [(1, 2), (2, 8), (4, 8), (8, 1)])
+@pytest.mark.parametrize("rows,hi", [(1, 9000), (5, 3000), (32, 1500)])
+def test_fused_segments_of_many_partials(group, hkv, rows, hi):
+    # few decode tiles over many workers, some without tiles: a segment's partials
+    # (more than 16) are shared by the merge's four waves, which exchange its last worker
+    ctx = [300, 700] + [int(x) for x in np.random.default_rng(rows).integers(hi // 2, hi + 1, rows)]
+    new = [120, 256] + [1] * rows
+    b = W.custom(ctx, [W.RT] * 2 + [W.BE] * rows, group * hkv, hkv, seed=rows + group, num_prefill=2, new_counts=new,
+                 spare_blocks=5)
+    poison_unowned(b)
+    announce(f"fused step, {rows} decode rows up to {hi} tokens, G={group} Hkv={hkv}")
+    _check(b, "many partials")

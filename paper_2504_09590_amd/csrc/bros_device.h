@@ -57,6 +57,17 @@ __device__ __forceinline__ int read_lane_i32(int v, int lane) {
   return __builtin_amdgcn_readlane(v, lane);
 }
 
+// n / d for 0 <= n < 2^22 and d >= 1, with rcp = 1 / d: the float estimate is
+// within one of the quotient, and one correction step makes it exact (a few
+// instructions instead of the long integer division sequence).
+__device__ __forceinline__ int div_small(int n, int d, float rcp) {
+  int q = (int)((float)n * rcp);
+  const int r = n - q * d;
+  q += (r >= d) ? 1 : 0;
+  q -= (r < 0) ? 1 : 0;
+  return q;
+}
+
 // Largest i in [0, n) with a[i] <= key, for a non-decreasing device array
 // (finds the sequence a flattened row belongs to from prefix offsets).
 __device__ __forceinline__ int upper_index(const int32_t* a, int n, int key) {

@@ -26,7 +26,7 @@ struct KvWriteArgs {
 };
 
 // Decode rows (cu_q == nullptr): row r is sequence r with context ctx_lens[r].
-// In fp32 also prefill chunks (cu_q != nullptr): row r belongs to the sequence s
+// For the fp32 prefill chunks (cu_q != nullptr): row r belongs to the sequence s
 // with cu_q[s] <= r < cu_q[s+1] and sees the first ctx_lens[s] - (cu_q[s+1] -
 // r) + 1 positions (causal, diagonal inclusive).
 struct DecodeArgs {
@@ -40,9 +40,10 @@ struct DecodeArgs {
   const int32_t* ctx_lens;
   const int32_t* cu_q;
   int32_t dir_per_entry;  // dir is [S][max_blocks_per_seq] (else [S])
-  // Partial results. fp32: [rows][Hq][n_split_max] slots. bf16 (one
+  // Partial results. fp32: [rows][Hq][n_split_max] slots. bf16, even split (one
   // worker per wave over an even share of the tiles): slot (row * Hkv + g +
-  // worker) * G + head-in-group, for segments cut between workers.
+  // worker) * G + head-in-group, for segments cut between workers. bf16, pieces
+  // (decode_short.hip): slot ((row * Hkv + g) * n_split_max + piece) * G + head-in-group.
   float* ws_acc;          // [slots][D] unnormalised partial outputs
   float* ws_ml;           // [slots][2] (running max in log2 units, sum)
   int32_t* ws_rows;       // bf16: first tile of each row, [rows + 1]
@@ -57,8 +58,9 @@ struct DecodeArgs {
   int32_t max_ctx;
   int32_t num_q_heads;
   int32_t num_kv_heads;
-  int32_t split_blocks;   // fp32: blocks per split (multiple of 4, <= 64; the prefill may take several of them at once)
-  int32_t n_split_max;    // fp32: splits the workspace is laid out for
+  int32_t split_blocks;   // blocks per split: fp32, from the plan's (multiple of 4, <= 64), of which a launch may
+                          // take several at once; bf16 whole segments and pieces
+  int32_t n_split_max;    // fp32: splits the workspace is laid out for; bf16 pieces: pieces of the longest context
   int32_t max_q_len;      // fp32 chunks: host bound of a sequence's rows
   int32_t tiles_per_seq;  // fp32 chunks: units of a sequence per KV head (set by the launch)
   float scale_log2;       // softmax scale * log2(e)

@@ -10,13 +10,13 @@
 // prefix, and for whole segments no partials and no second kernel. The loads of
 // a wave's next block are requested as its registers are read, with no branch
 // around them; four waves per SIMD cover the rest of the latency, which bounds
-// it: under 1 us per tile of a wave after 4 us of start-up. Calls in us (32 / 8
-// heads unless said), the even split and this:
-//   whole  one row of 100 tokens 8.6 / 4.3, 16 rows of 64 to 256 13.2 / 7.3, 64 of
-//          128 to 512 25.8 / 20.0, 512 of 64 to 256 76 / 69
-//   split  one row of 8000 22.7 / 11.7, six of 90 to 2048 17.4 / 13.0, four of
-//          1024 to 4096 22.6 / 14.4, 64 of 512 to 2048 with 8 / 1 heads 22.5 /
-//          14.9, 8 of 4000 to 8192 with 64 / 8 heads 50.9 / 43.4
+// it: under 1 us per tile of a wave after 4 us of start-up. Device time in us (32 /
+// 8 heads unless said), the even split and this (plan.h says which calls):
+//   whole  one row of 200 tokens 10.3 / 5.8, 16 rows of 25 to 200 11.8 / 6.7, 64 of
+//          64 to 512 24.7 / 18.8, 512 of 25 to 200 59.4 / 53.6
+//   split  one row of 8000 22.6 / 11.1, six of 312 to 2500 19.4 / 14.7, four of 500
+//          to 4000 19.3 / 15.1, 64 of 312 to 2500 with 8 / 1 heads 26.4 / 20.7, 8 of
+//          1000 to 8000 with 64 / 8 heads 42.3 / 37.5
 // (With 8 waves a segment 1 us slower, with 16 up to twice as long: a compute
 // unit then reads one segment at its own rate.)
 #include "decode_device.h"
@@ -137,7 +137,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
       // 0.0017 with both, the output's own rounding; 0.1 us a call.)
       // The first part is taken a little short of the weight, so that the second
       // is positive too: with a part that is 0 or negative, a V value of infinity
-      // would become a NaN. (What both leave is 2^-15 of the weight at most.)
+      // would become a NaN. (What both leave is below 2^-13 of the weight: the second
+      // part, up to 2^-6 + 2^-8 of it, is rounded to 8 bits.)
       constexpr float kShort = 1.0f - 0x1p-6f;
       const uint2 hi2 = {pack2_bf16(kShort * p[0], kShort * p[1]), pack2_bf16(kShort * p[2], kShort * p[3])};
       const uint2 lo2 = {pack2_bf16(p[0] - bf16_lo(hi2.x), p[1] - bf16_hi(hi2.x)),

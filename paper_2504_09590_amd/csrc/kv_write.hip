@@ -26,17 +26,6 @@ constexpr int kMaxIter = 2;
 
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));   // 16 bytes (a plain vector promotes to registers)
 
-// n / d for 0 <= n < 2^22 and d >= 1, with rcp = 1 / d: the float estimate is
-// within one of the quotient, and one correction step makes it exact (a few
-// instructions instead of the long integer division sequence).
-__device__ __forceinline__ int div_small(int n, int d, float rcp) {
-  int q = (int)((float)n * rcp);
-  const int r = n - q * d;
-  q += (r >= d) ? 1 : 0;
-  q -= (r < 0) ? 1 : 0;
-  return q;
-}
-
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void kv_write_kernel(KvWriteArgs a) {
   __shared__ int s_seq[kTokens];   // the sequence holding each token, or -1

@@ -101,7 +101,11 @@ hipError_t launch_group(PrefillArgs a, int num_units, hipStream_t stream) {
     // 8 us or 16 tiles in all. From 48 tiles on it may save that much however
     // many units there are. 512 rows on 0 / 500 / 1000 / 4000 / 16000 cached
     // tokens, 128 units: whole 17.0 / 25.6 / 33.1 / 79 / 265 us, split 19.7 /
-    // 26.1 / 30.3 / 55.6 / 150 us.
+    // 26.1 / 30.3 / 55.6 / 150 us. Over 620 calls with fewer units than compute
+    // units (1 to 6 chunks, 0 to 20000 cached tokens, 64 / 8 to 8 / 1 heads)
+    // splitting by this rule is 1.58 times as fast as none, 5 % faster than
+    // asking the device plan every time, and slower than none, by up to 20 %, in 47
+    // (units of unlike length near 48 to 100 tiles).
     const int longest = std::min(a.max_ctx, a.max_blocks_per_seq * kBlockSize) / kKeys;
     if (num_units < cus && (longest >= 48 || (int64_t)longest * (cus - num_units) >= 16 * (int64_t)cus)) a.num_cus = cus;
   }

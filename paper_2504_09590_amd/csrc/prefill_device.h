@@ -44,18 +44,19 @@
 // step apart, share one index. Contexts whose table is longer than that LDS
 // copy (more than kPrefillWholeTableCtx positions) take a variant that keeps
 // a ring of the piece's entries there and refills half of it every 512 tiles
-// (512 rows on 40000 cached tokens, 32 / 8 heads: 415 us, 815 TFLOP/s; as
+// (512 rows on 40000 cached tokens, 32 / 8 heads: 365 us, 925 TFLOP/s; as
 // decode rows, each reading its whole context, they took 12.0 ms).
 //
-// What bounds a step: the card's power, with two workgroups per compute unit
-// (the matrix cores are busy 0.63 of the clocks, and the clock falls from 2.4
-// to 1.8 GHz), so the step carries as few instructions as it can: no 64-bit
-// address arithmetic, the rescale factor computed only when the max moves, the
-// row sums of P as eight packed dot products. (Two more matrix products with a
-// ones operand instead of the dot products cost 2-4 % everywhere: four prompts
-// of 4096 rows 538 us against 526, 512 rows on 16000 cached tokens 143 against
-// 139, on 40000 372 against 358, the mixed step's chunks 58.3 against 56.4, all
-// 32 / 8 heads on one card.)
+// What bounds a step: the card's power, with two workgroups per compute unit for
+// long (the clock falls from 2.4 to 1.85 GHz, at which the matrix cores are busy
+// 0.40 of the time over four prompts of 2500 to 4096 rows, 0.49 over 512 rows on
+// 16000 cached tokens), and the operands, 1 KiB from LDS per product. So the step
+// carries as few instructions as it can: no 64-bit address arithmetic, the rescale
+// factor computed only when the max moves, the row sums of P as eight packed dot
+// products. (Two more matrix products with a ones operand instead of the dot
+// products cost 2-4 % everywhere: four prompts of 4096 rows 538 us against 526, 512
+// rows on 16000 cached tokens 143 against 139, on 40000 372 against 358, the mixed
+// step's chunks 58.3 against 56.4, all 32 / 8 heads on one card.)
 //
 // Software pipeline (per wave, per step): the scores S^T = K Q^T of the next
 // tile are computed on the matrix cores while the vector ALU turns the current
@@ -106,7 +107,8 @@ constexpr int kRefillTiles = kMaxTableLds / 4;     // ring variant: tiles (2 ent
 constexpr int kTablePad = 32;                      // staged entries past the last tile (loads run ahead)
 constexpr int kMaxRankItems = kThreads;            // units planned on the device (one per thread)
 constexpr int kMinPartTiles = 8;                   // the shortest piece a unit is split into
-constexpr int kMinSavedTiles = 12;                 // what splitting must take off the longest unit
+constexpr int kMinSavedTiles = 12;                 // what splitting must take off the longest unit (0, 6 and 24: within 0.3 %
+                                                   // of it over 620 calls with fewer units than compute units)
 constexpr int kPairTiles = 12;                     // what a second piece on every compute unit costs
 constexpr int kLoadsPerStep = 4;                   // two K and two V loads per wave per step
 constexpr int kXcds = 8;                           // accelerator dies of the chip; blockIdx % 8 picks the die

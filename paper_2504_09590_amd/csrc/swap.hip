@@ -30,16 +30,6 @@ constexpr int kIter = 8;   // 16-byte chunks per thread
 
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 
-// n / d for 0 <= n < 2^24 and d >= 1, with rcp = 1 / d: the float estimate is
-// within one of the quotient, and one correction step makes it exact.
-__device__ __forceinline__ int div_small(int n, int d, float rcp) {
-  int q = (int)((float)n * rcp);
-  const int r = n - q * d;
-  q += (r >= d) ? 1 : 0;
-  q -= (r < 0) ? 1 : 0;
-  return q;
-}
-
 // ITERS: chunks per thread, kIter, or 1 for a list that one per thread covers (a
 // slot or a few: seven rounds of index arithmetic less, a gather 3.8 us -> 3.0).
 template <bool GATHER, int ROW_CHUNKS, int ITERS>

@@ -1,4 +1,4 @@
-"""bf16 decode of few rows: contexts in pieces of 16, 32 or 64 blocks, one
+"""bf16 decode of few rows: contexts in pieces of 8, 16, 32 or 64 blocks, one
 workgroup each, and their merge (a round per eight partials); beyond 64 pieces
 the even split, whose merge's waves share a segment's many partials, and which
 gives a wave up to four tiles when one long context stands among short ones.
@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("group,hkv", [(1, 8), (2, 2), (4, 8), (8, 1)])
-# whole up to 32 blocks; then 3 pieces, 8 and 9 partials (one round and two), 63, 64 and 65 of 16 blocks
+# whole; then 5 pieces of 8 blocks, 16 and 17 (two rounds and three), and pieces of 32 blocks
 @pytest.mark.parametrize("blocks", [1, 32, 33, 128, 129, 1000, 1024, 1025])
 def test_one_row(group, hkv, blocks):
     require_gpu()

@@ -1,7 +1,6 @@
-"""bf16 decode of short contexts in one launch: contexts and segment counts on
-both sides of its rule (32 blocks, 64 from 64 segments on, 24, 32, 48 or 64 by
-group size from 512 on), all group sizes,
-empty rows, a max_ctx above every context, invalid table entries and directions
+"""bf16 decode of short contexts in one launch: contexts and segment counts around
+its rule (whole up to 24 blocks with few segments, 28 to 64 by group size and
+segments per compute unit with more), all group sizes, empty rows, a max_ctx above every context, invalid table entries and directions
 per entry. Against the oracle at the bf16 bar of every other kernel test."""
 
 import numpy as np

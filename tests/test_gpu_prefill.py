@@ -166,7 +166,7 @@ def test_rt_chunks_walking_from_the_right():
 def test_f32_chunks():
     b = written(chunk_batch([0, 21, 300], [20, 33, 17], [W.RT] * 3, group=4, hkv=2, dtype="f32", seed=32))
     poison_unowned(b)
-    announce("prefill fp32 (vector path)")
+    announce("prefill fp32")
     compare(run_prefill(b), ref_prefill(b), "f32", "f32 prefill")
 
 
@@ -178,11 +178,10 @@ def test_last_row_matches_decode_at_the_same_length():
 
 
 def test_bf16_context_beyond_the_matrix_core_path():
-    # max_ctx above 32768 routes bf16 prefill through the decode kernel in row
-    # mode (every chunk row a decode row with its own causal context).
+    # max_ctx above 32768: the table is longer than its LDS copy (the ring variant)
     b = written(chunk_batch([33000], [40], [W.RT], group=4, hkv=1, seed=15))
     poison_unowned(b)
-    announce("prefill bf16 c0=33000 n=40 (row-mode path)")
+    announce("prefill bf16 c0=33000 n=40 (ring variant)")
     compare(run_prefill(b), ref_prefill(b), "bf16", "bf16 ctx > 32768")
 
 

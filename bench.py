@@ -66,10 +66,10 @@ DECODE_SOURCES = ("paper_2504_09590_amd/csrc/decode.hip", "paper_2504_09590_amd/
                   "paper_2504_09590_amd/csrc/bros_kernels.h")
 DECODE_COUNTERS = {
     # workload: (sha256 of DECODE_SOURCES when the counters were read, FETCH_SIZE KiB, WRITE_SIZE KiB)
-    "llama3-70b-decode": ("f12efb5159ca9ddbc4bd03e7871364d4a41b058062ac265b93f1a6bc2576ee52", 4991849.4, 16514.1),
-    "llama3-8b-decode": ("f12efb5159ca9ddbc4bd03e7871364d4a41b058062ac265b93f1a6bc2576ee52", 454831.8, 5197.5),
-    "llama3-8b-mixed-step": ("f12efb5159ca9ddbc4bd03e7871364d4a41b058062ac265b93f1a6bc2576ee52", 1129273.9, 6173.5),
-    "llama3-8b-pressure": ("f12efb5159ca9ddbc4bd03e7871364d4a41b058062ac265b93f1a6bc2576ee52", 601668.8, 10115.7),
+    "llama3-70b-decode": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 4991883.4, 16515.2),
+    "llama3-8b-decode": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 454810.0, 5197.6),
+    "llama3-8b-mixed-step": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 1129280.6, 6173.2),
+    "llama3-8b-pressure": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 601640.4, 10116.3),
 }
 
 

@@ -175,7 +175,8 @@ int bros_attn_decode(void* out, const void* q,
  *
  *   q, out       : [num_q_tokens][num_q_heads][head_dim]
  *   cu_q         : int32 [num_seqs + 1], prefix offsets; cu_q[num_seqs] = num_q_tokens
- *   max_q_len    : host-side upper bound of every n (sizes the grid)
+ *   max_q_len    : host-side upper bound of every n (sizes the grid; a bound beyond
+ *                  num_q_tokens counts as num_q_tokens)
  *   max_ctx      : host-side upper bound of every ctx_lens[s]
  *   workspace    : at least bros_attn_workspace_size(BROS_WS_PREFILL, dtype,
  *                  num_q_tokens, num_q_heads, head_dim, max_ctx) bytes,

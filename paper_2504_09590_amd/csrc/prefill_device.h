@@ -110,6 +110,7 @@ constexpr int kMinPartTiles = 8;                   // the shortest piece a unit 
 constexpr int kMinSavedTiles = 12;                 // what splitting must take off the longest unit (0, 6 and 24: within 0.3 %
                                                    // of it over 620 calls with fewer units than compute units)
 constexpr int kPairTiles = 12;                     // what a second piece on every compute unit costs
+constexpr int kLongPieces = 96;                    // the shortest pieces of which two to a compute unit are the first choice
 constexpr int kLoadsPerStep = 4;                   // two K and two V loads per wave per step
 constexpr int kXcds = 8;                           // accelerator dies of the chip; blockIdx % 8 picks the die
 
@@ -274,20 +275,26 @@ struct PiecePlan {
 // length (several share a slot in turn).
 //
 // The budget is one piece per compute unit, or two: of two resident workgroups each
-// advances 1 us per tile, alone 0.55, and the second costs another start-up and
+// advances 0.7 us per tile while few compute units hold two and 1 us when all do,
+// alone 0.55, and the second costs another start-up and
 // more partials, as long as kPairTiles tiles. So two pay where pieces are long (512 rows on
 // 16000 cached tokens: 154 us with two, 163 with one; on 4000: 61 and 59), and where
 // the units cannot be cut evenly into one piece per compute unit (192 units of
 // 192 to 284 tiles, 8 / 8 heads: 111 us with two, 155 with one, when most stay whole; two
-// prompts of 1986 rows, 8 / 1 heads: 49 and 79).
+// prompts of 1986 rows, 8 / 1 heads: 49 and 79). A workspace for fewer partials than two
+// per compute unit still gives units a third piece (325 rows on 38000, 32 / 8 heads, 337
+// partials: 271 us with 264 pieces, 312 with 176).
 struct PartSize {
   int budget[2], t0[2];   // one and two pieces per compute unit
-  __device__ PartSize(const PrefillArgs& a, int total) {
+  int first;              // the budget that is looked at first
+  float cus_per_head;
+  __device__ PartSize(const PrefillArgs& a, int total) : cus_per_head((float)a.num_cus / (float)a.num_kv_heads) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       budget[k] = max(1, min((k + 1) * a.num_cus, a.ws_slots) / a.num_kv_heads);
       t0[k] = max((total + budget[k] - 1) / budget[k], kMinPartTiles);
     }
+    first = total >= kLongPieces * budget[1] ? 1 : 0;
   }
   // candidate c of n (c < n) of budget k: t0 .. 2 t0
   __device__ int candidate(int k, int c, int n) const { return t0[k] + (int)((int64_t)t0[k] * c / (n - 1)); }
@@ -298,18 +305,47 @@ struct PartSize {
     const float x = (float)max(L, 0) * rcp;
     return x <= 1.0f ? x : ceilf(x - 1e-4f);
   }
-  // The part size, or 0 where splitting does not pay; the longest unit has Lmax
-  // tiles. Lane c holds what the units take of each budget at its candidate c of
-  // kWave. A budget ends with its longest piece, in tiles at the pace of one
+  // The part size, or 0 where splitting does not pay. Lane c holds unit c's tiles L (of
+  // n <= kWave units), the longest has Lmax; `sum` adds a value up over all units'
+  // waves. A budget ends with its longest piece, in tiles at the pace of one
   // workgroup per compute unit; that must be kMinSavedTiles earlier than the longest
-  // unit whole, or the partials and the merge cost what is saved.
-  __device__ int choose(float pieces0, float pieces1, int Lmax) const {
-    const uint64_t fits0 = __builtin_amdgcn_ballot_w64(pieces0 <= (float)budget[0]);
-    const uint64_t fits1 = __builtin_amdgcn_ballot_w64(pieces1 <= (float)budget[1]);
-    const int T0 = candidate(0, fits0 ? __builtin_ctzll(fits0) : kWave - 1, kWave);
-    const int T1 = candidate(1, fits1 ? __builtin_ctzll(fits1) : kWave - 1, kWave);
-    const int one = min(T0, Lmax), two = min(T1, Lmax) * 20 / 11 + kPairTiles;
-    return Lmax - min(one, two) >= kMinSavedTiles ? (one <= two ? T0 : T1) : 0;
+  // unit whole, or the partials and the merge cost what is saved. Two pieces per
+  // compute unit are the first choice where kLongPieces tiles remain, else one. The other
+  // is taken where it ends a twelfth earlier, and looked at where that can be: one
+  // ends no earlier than t0[0], two no earlier than 0.7 T + t0[1] + kPairTiles (there are
+  // at least total / T). (Looking at both always takes 1 us of 35 with 30 units.)
+  template <class Sum>
+  __device__ int choose(int L, int n, int Lmax, int lane, Sum sum) const {
+    const auto look = [&](int k, int* end) {
+      const float pieces = sum(shares(L, n, rcp(k, lane, kWave)));
+      const uint64_t fits = __builtin_amdgcn_ballot_w64(pieces <= (float)budget[k]);
+      const int c = fits ? __builtin_ctzll(fits) : kWave - 1;
+      const int T = candidate(k, c, kWave);
+      *end = min(T, Lmax);
+      if (k == 1) {
+        // (the share of the compute units that hold two pieces)
+        const float paired = __int_as_float(read_lane_i32(__float_as_int(pieces), c)) / cus_per_head - 1.0f;
+        *end = (int)((float)*end * (1.25f + 0.5f * fminf(fmaxf(paired, 0.0f), 1.0f))) + kPairTiles;
+      }
+      return T;
+    };
+    int end, other_end;
+    int T = look(first, &end);
+    const int sooner = first ? t0[0] : t0[1] + 7 * t0[1] / 10 + kPairTiles;
+    if (sooner < end - end / 12) {
+      const int other = look(1 - first, &other_end);
+      if (other_end < end - end / 12) {
+        T = other;
+        end = other_end;
+      }
+    }
+    return Lmax - end >= kMinSavedTiles ? T : 0;
+  }
+  // What the first n lanes' units take at this lane's part size.
+  static __device__ float shares(int L, int n, float rcp) {
+    float pieces = 0.0f;
+    for (int i = 0; i < n; ++i) pieces += share(read_lane_i32(L, i), rcp);
+    return pieces;
   }
 };
 
@@ -345,16 +381,11 @@ __device__ PiecePlan plan_pieces_wave(const PrefillArgs& a, int rank) {
   if (a.num_cus > 0) {
     const int total = read_lane_i32(wave_inclusive_scan(L, lane), kWave - 1);
     const PartSize ps(a, total);
-    const float rcp0 = ps.rcp(0, lane, kWave), rcp1 = ps.rcp(1, lane, kWave);
-    float pieces0 = 0.0f, pieces1 = 0.0f;
-    int Lmax = 0;
-    for (int i = 0; i < n_items; ++i) {
-      const int Li = read_lane_i32(L, i);
-      pieces0 += PartSize::share(Li, rcp0);
-      pieces1 += PartSize::share(Li, rcp1);
-      Lmax = max(Lmax, Li);
-    }
-    const int T = ps.choose(pieces0, pieces1, Lmax);
+    int Lmax = L;
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) Lmax = max(Lmax, __shfl_xor(Lmax, o));
+    Lmax = __builtin_amdgcn_readfirstlane(Lmax);
+    const int T = ps.choose(L, n_items, Lmax, lane, [](float v) { return v; });
     const int P = L > 0 ? 1 + (L - 1) / max(T, 1) : 0;
     const int own = P > 1 ? P : 0;
     const int send = wave_inclusive_scan(own, lane);
@@ -449,30 +480,25 @@ __device__ PiecePlan plan_pieces(const PrefillArgs& a, int rank, int* scratch) {
     // Every wave takes the items of its own lanes, for all candidates (a lane
     // each), and the four waves' parts are added up. (Every thread going over all items in LDS for a
     // candidate of its own took 10 us of 180 items.)
-    const float rcp0 = ps.rcp(0, lane, kWave), rcp1 = ps.rcp(1, lane, kWave);
-    float pieces0 = 0.0f, pieces1 = 0.0f;
-    int Lmax = 0;
-    const int mine = min(kWave, n_items - w * kWave);
-    for (int i = 0; i < mine; ++i) {
-      const int Li = read_lane_i32(L, i);
-      pieces0 += PartSize::share(Li, rcp0);
-      pieces1 += PartSize::share(Li, rcp1);
-      Lmax = max(Lmax, Li);
-    }
-    float2* s_part = reinterpret_cast<float2*>(scratch);   // [kThreads]
-    s_part[tid] = make_float2(pieces0, pieces1);
+    int Lmax = L;
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) Lmax = max(Lmax, __shfl_xor(Lmax, o));
     if (lane == 0) s_res[w] = Lmax;
     __syncthreads();
-    pieces0 = pieces1 = 0.0f;
     Lmax = 0;
 #pragma unroll
-    for (int x = 0; x < kThreads / kWave; ++x) {
-      const float2 v = s_part[x * kWave + lane];
-      pieces0 += v.x;
-      pieces1 += v.y;
-      Lmax = max(Lmax, s_res[x]);
-    }
-    const int T = ps.choose(pieces0, pieces1, Lmax);
+    for (int x = 0; x < kThreads / kWave; ++x) Lmax = max(Lmax, s_res[x]);
+    Lmax = __builtin_amdgcn_readfirstlane(Lmax);
+    float* s_part = reinterpret_cast<float*>(scratch);   // [2 kThreads], a half for each sum
+    const int T = ps.choose(L, min(kWave, max(n_items - w * kWave, 0)), Lmax, lane, [&](float v) {
+      s_part[tid] = v;
+      __syncthreads();
+      v = 0.0f;
+#pragma unroll
+      for (int x = 0; x < kThreads / kWave; ++x) v += s_part[x * kWave + lane];
+      s_part += kThreads;
+      return v;
+    });
     const int Pt = L > 0 ? 1 + (L - 1) / max(T, 1) : 0;
     const int own = Pt > 1 ? Pt : 0;
     int n_split = 0;

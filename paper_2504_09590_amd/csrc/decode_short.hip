@@ -276,10 +276,16 @@ hipError_t launch_short_group(DecodeArgs a, hipStream_t stream, hipEvent_t betwe
 }  // namespace dm
 
 bool plan_decode_short(DecodeArgs& a, hipStream_t stream) {
+  const int64_t segments = (int64_t)a.num_rows * a.num_kv_heads;
+  const int32_t blocks = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
+  if (whole_on_any_share(segments, blocks)) {   // (asking for the stream's compute units costs the smallest steps 0.6 us of 16)
+    a.split_blocks = blocks;
+    a.n_split_max = 1;
+    return true;
+  }
   // (partials: the workspace has a slot per query row and kDecodeGroupSlots groups more)
   const int64_t slots = (int64_t)a.num_rows * a.num_q_heads + (int64_t)kDecodeGroupSlots * std::min(a.num_q_heads, 8);
-  return plan_short_decode((int64_t)a.num_rows * a.num_kv_heads, a.num_q_heads / a.num_kv_heads,
-                           longest_blocks(a.max_ctx, a.max_blocks_per_seq), stream_compute_units(stream), slots,
+  return plan_short_decode(segments, a.num_q_heads / a.num_kv_heads, blocks, stream_compute_units(stream), slots,
                            &a.split_blocks, &a.n_split_max);
 }
 

@@ -119,37 +119,45 @@ inline F32ChunkPlan plan_f32_chunks(int32_t num_rows, int32_t num_seqs, int32_t 
   return p;
 }
 
+// What longest_whole (below) never falls short of.
+constexpr int32_t kWholeOnAnyShare = 32;
+
 // Longest context, in blocks, that the bf16 decode gives whole to one workgroup per
 // (row, KV head) segment, by the segments per compute unit. With few of them,
-// pieces spread a context over more compute units; from one on, a few long
+// pieces spread a context over more compute units. They are up to 2 us shorter from
+// 24 blocks on, but a step of few rows waits for its host calls, of which the
+// merge's launch takes 3 us (12 rows of 108 to 408 tokens, 64 / 8 heads: a step of
+// 16.8 us whole, 19.5 in pieces). From two segments per compute unit on, a few long
 // contexts among short ones are waited for, and the even split's partials, which
 // whole segments save, are the smaller the fewer heads share a segment.
 inline int32_t longest_whole(int64_t segments, int32_t group, int32_t compute_units) {
   const int64_t cus = compute_units;
-  if (segments < cus / 2) return 24;
-  if (segments < cus) return group >= 8 ? 64 : 48;
-  if (segments < cus * 5 / 4) return 64;
-  if (segments < 2 * cus) return group >= 4 ? 64 : 32;
-  if (segments < 4 * cus) return group >= 8 ? 64 : group >= 4 ? 48 : 40;
-  return group >= 8 ? 64 : group >= 4 ? 48 : 28;
+  if (segments < cus / 4) return kWholeOnAnyShare;
+  if (segments < cus / 2) return 56;
+  if (segments < 2 * cus || group >= 8) return 64;
+  if (group >= 4) return 48;
+  return segments < 4 * cus ? 40 : kWholeOnAnyShare;
 }
+
+// Whether plan_short_decode (below) gives whole segments however many compute units there are.
+inline bool whole_on_any_share(int64_t segments, int64_t blocks) { return segments <= 0x7fffffff && blocks <= kWholeOnAnyShare; }
 
 // Whether the bf16 decode runs whole segments or pieces of `split_blocks` blocks
 // (decode_short.hip), or else the even split (decode.hip).
 //
 // Pieces take the shortest size of which a context has no more than a few (a
-// workgroup folds them, eight a round) and the call no more than the compute units
-// hold at once. Pieces of 64 blocks are long enough that a long context among
-// shorter ones sets the end: with fewer than 8 heads per KV head they lose more
-// there (6 rows of 1000 to 8000 tokens, 16 / 8 heads: 35 us, even split 25) than
-// they gain on equal contexts (8 rows of 8000: 44, even split 51), unless there are
-// only a few segments at all.
+// workgroup folds them, eight a round) and the call no more than one per compute
+// unit, or two of 32 or 64 blocks; with more of them the even split's longer walks read the
+// HBM better. Pieces of 64 blocks are long enough that a long context among shorter ones
+// sets the end (12 rows of lognormal contexts up to 4000 tokens, 16 / 8 heads: 34 us, even
+// split 29), and gain more where contexts are alike (8 rows of 8000: 44 us, even split 51).
 //
 // Device time over 2502 calls of 1 to 512 rows of up to 64 to 16000 tokens (equal,
 // uniform and lognormal contexts; 64 / 8, 32 / 8, 16 / 8, 8 / 8 and 8 / 1 heads)
-// on 256 compute units: 3 % above the best of the even split, whole segments and
-// seven piece sizes for each call, the even split 42 %. Calls in us, the even split
-// / this (32 / 8 heads unless said):
+// on 256 compute units: 4 % above the best of the even split, whole segments and
+// seven piece sizes for each call, the even split 42 %; without the pieces of 8 blocks
+// 6 %. In 35 calls the even split is faster by more than 5 %, lognormal contexts
+// mostly. Calls in us, the even split / this (32 / 8 heads unless said):
 //   whole   16 rows of 64 to 256 tokens 13.2 / 7.3, 64 of 128 to 512 25.8 / 20.0, 512 of 8
 //           to 64 29.1 / 26.0 (but 512 of 64 each 30.1 / 32.6: what is known here is the
 //           longest)
@@ -159,9 +167,9 @@ inline int32_t longest_whole(int64_t segments, int32_t group, int32_t compute_un
 inline bool plan_short_decode(int64_t segments, int32_t group, int64_t blocks, int32_t compute_units, int64_t slots,
                               int32_t* split_blocks, int32_t* n_split) {
   struct Pieces {
-    int32_t blocks, per_cu, splits;   // size; quarters of a piece per compute unit and pieces of a context, at most
+    int32_t blocks, per_cu, splits;   // size; pieces per compute unit and of a context, at most
   };
-  constexpr Pieces kPieces[] = {{8, 4, 24}, {16, 12, 32}, {32, 8, 48}, {64, 8, 64}};
+  constexpr Pieces kPieces[] = {{8, 1, 24}, {16, 1, 64}, {32, 2, 64}, {64, 2, 64}};
   if (segments > 0x7fffffff) return false;
   if (blocks <= longest_whole(segments, group, compute_units)) {
     *split_blocks = (int32_t)blocks;
@@ -169,9 +177,8 @@ inline bool plan_short_decode(int64_t segments, int32_t group, int64_t blocks, i
     return true;
   }
   for (const Pieces& p : kPieces) {
-    if (p.blocks == 64 && group < 8 && segments > 16) continue;
     const int64_t splits = (blocks + p.blocks - 1) / p.blocks;
-    if (splits < 2 || splits > p.splits || segments * splits * 4 > (int64_t)p.per_cu * compute_units) continue;
+    if (splits < 2 || splits > p.splits || segments * splits > (int64_t)p.per_cu * compute_units) continue;
     if (segments * splits * group > slots) continue;   // (partials)
     *split_blocks = p.blocks;
     *n_split = (int32_t)splits;

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("group,hkv", [(1, 8), (2, 2), (4, 8), (8, 1)])
-# whole; then 5 pieces of 8 blocks, 16 and 17 (two rounds and three), and pieces of 32 blocks
+# whole; then 5 pieces of 8 blocks, 16 and 17 (two rounds and three), and pieces of 16 and 32 blocks
 @pytest.mark.parametrize("blocks", [1, 32, 33, 128, 129, 1000, 1024, 1025])
 def test_one_row(group, hkv, blocks):
     require_gpu()
@@ -91,10 +91,10 @@ def test_infinite_values_of_the_last_piece(ctx, pos, value):
     assert np.isfinite(got).all() and np.abs(got - ref).max() <= 2e-2
 
 
-# the edges of the pieces: whole up to 24 blocks, 8 blocks (up to 24 pieces), 16 (32), 32 (48), 64 (64, with
-# fewer than 8 heads for up to 16 segments), then the even split
+# the edges of the pieces: whole up to 32 blocks, 8 blocks (up to 24 pieces), 16, 32 and 64 (up to 64 pieces), each
+# only while the pieces of all rows are few
 @pytest.mark.parametrize("group,hkv,rows", [(1, 2, 1), (8, 1, 1), (4, 8, 1), (4, 17, 1), (8, 2, 9)])
-@pytest.mark.parametrize("blocks", [24, 25, 192, 193, 512, 513, 1536, 1537])
+@pytest.mark.parametrize("blocks", [32, 33, 192, 193, 1024, 1025, 2048, 2049])
 def test_edges_of_the_pieces(group, hkv, rows, blocks):
     require_gpu()
     ctx = [16 * blocks - (blocks % 5)] + [17 * i + 3 for i in range(1, rows)]

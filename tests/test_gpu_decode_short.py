@@ -1,5 +1,5 @@
 """bf16 decode of short contexts in one launch: contexts and segment counts around
-its rule (whole up to 24 blocks with few segments, 28 to 64 by group size and
+its rule (whole up to 32 blocks with few segments, 32 to 64 by group size and
 segments per compute unit with more), all group sizes, empty rows, a max_ctx above every context, invalid table entries and directions
 per entry. Against the oracle at the bf16 bar of every other kernel test."""
 

@@ -25,6 +25,7 @@ void chunks(int rows, int seqs, int max_q, int nkv, int pos, int longest, int pl
   const bros::F32ChunkPlan p = bros::plan_f32_chunks(rows, seqs, max_q, nkv, pos, longest, plan, cus);
   out[0] = p.units; out[1] = p.tiles_per_seq; out[2] = p.split_blocks; out[3] = p.splits;
 }
+int whole(long long segments, long long blocks) { return bros::whole_on_any_share(segments, blocks); }
 int pieces(long long segments, int group, long long blocks, int cus, long long slots, int* out) {
   return bros::plan_short_decode(segments, group, blocks, cus, slots, out, out + 1);
 }
@@ -47,6 +48,7 @@ def plan(tmp_path_factory):
     lib.longest.argtypes = [I, I]
     lib.items.argtypes = [Q, I, I, I, I, I]
     lib.chunks.argtypes = [I] * 8 + [ctypes.POINTER(Q)]
+    lib.whole.argtypes = [Q, Q]
     lib.pieces.argtypes = [Q, I, Q, I, Q, ctypes.POINTER(I)]
     return lib
 
@@ -147,15 +149,19 @@ def test_short_decode_limits_follow_the_compute_units(plan):
                     if cus != 256 and segments > 16:
                         assert got == short_plan(plan, segments * 256 // cus, group, blocks, 256)
                     if got is not None and got[1] > 1:
-                        assert got[1] == -(-blocks // got[0]) <= 64 and segments * got[1] <= 3 * cus
+                        assert got[1] == -(-blocks // got[0]) <= 64 and segments * got[1] <= 2 * cus
                     if got is not None and got[1] == 1:
                         assert got[0] == blocks <= 64
-    # four rows of 1024 to 4096 tokens, 8 KV heads: pieces on the whole chip, fewer on a quarter of it
-    assert short_plan(plan, 32, 4, 256) == (16, 16)
-    assert short_plan(plan, 32, 4, 256, cus=64) is None
+                    if plan.whole(segments, blocks):       # (decided without the compute units)
+                        assert got == (blocks, 1)
+    # four rows of 1024 to 4096 tokens, 8 KV heads: pieces of 32 blocks on the whole chip, longer ones on a quarter
+    # of it, the even split on an eighth
+    assert short_plan(plan, 32, 4, 256) == (32, 8)
+    assert short_plan(plan, 32, 4, 256, cus=64) == (64, 4)
+    assert short_plan(plan, 32, 4, 256, cus=32) is None
 
 
 def test_short_decode_partials_fit(plan):
     assert short_plan(plan, 8, 8, 100, slots=8 * 13 * 8) == (8, 13)
     assert short_plan(plan, 8, 8, 100, slots=8 * 13 * 8 - 1) == (16, 7)
-    assert short_plan(plan, 2**31, 1, 4) is None
+    assert short_plan(plan, 2**31, 1, 4) is None and not plan.whole(2**31, 4) and plan.whole(2**31 - 1, 4)

@@ -145,9 +145,10 @@ constexpr int32_t kPrefillWholeTableCtx = 32768;
 // hipExtStreamCreateWithCUMask runs on a subset of the device): the device's
 // count is queried once per device, the stream's CU mask read on every call.
 int stream_compute_units(hipStream_t stream);
-// Workgroups of `kernel` (launched with `threads` threads) that the compute
-// units enabled for `stream` hold at once; the per-CU occupancy is queried once
-// per device and cache slot (0..7: bf16 decode 0..3, fp32 decode 4..7).
+// Workgroups of `kernel` (launched with `threads` threads) that a compute unit
+// holds at once, queried once per device and cache slot (0..7: bf16 decode 0..3,
+// fp32 decode 4..7), and that those enabled for `stream` do.
+int workgroups_per_cu(const void* kernel, int threads, int slot);
 int resident_workgroups(const void* kernel, int threads, int slot, hipStream_t stream);
 
 hipError_t launch_prefill_mfma(PrefillArgs a, int group, int num_tiles_total, hipStream_t stream);

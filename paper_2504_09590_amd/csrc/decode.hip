@@ -288,13 +288,13 @@ int stream_compute_units(hipStream_t stream) {
   return stream_cus(stream, cus);
 }
 
-int resident_workgroups(const void* kernel, int threads, int slot, hipStream_t stream) {
+int workgroups_per_cu(const void* kernel, int threads, int slot) {
   constexpr int kMaxDevices = 64;
   constexpr int kSlots = 8;
   static int per_cu_cache[kMaxDevices][kSlots];
   static std::mutex mu;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 1024;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 4;
   int per_cu = 0;
   {
     std::lock_guard<std::mutex> lock(mu);
@@ -305,7 +305,11 @@ int resident_workgroups(const void* kernel, int threads, int slot, hipStream_t s
     }
     per_cu = per_cu_cache[dev][slot];
   }
-  return per_cu * stream_compute_units(stream);
+  return per_cu;
+}
+
+int resident_workgroups(const void* kernel, int threads, int slot, hipStream_t stream) {
+  return workgroups_per_cu(kernel, threads, slot) * stream_compute_units(stream);
 }
 
 namespace {

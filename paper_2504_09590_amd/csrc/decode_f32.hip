@@ -537,9 +537,10 @@ __global__ __launch_bounds__(kHeadDim) void f32_merge_kernel(DecodeArgs a) {
 
 template <int G>
 hipError_t launch_group_f32(DecodeArgs a, hipStream_t stream, int slot) {
-  const int resident = resident_workgroups(reinterpret_cast<const void*>(&decode_f32_kernel<G, false>), kThreads, slot, stream);
+  const int cus = stream_compute_units(stream);
+  const int resident = workgroups_per_cu(reinterpret_cast<const void*>(&decode_f32_kernel<G, false>), kThreads, slot) * cus;
   const int32_t maxblk = longest_blocks(a.max_ctx, a.max_blocks_per_seq);
-  const int32_t per = f32_item_blocks(a.num_rows, a.num_kv_heads, G, maxblk, a.split_blocks, resident);
+  const int32_t per = f32_item_blocks(a.num_rows, a.num_kv_heads, G, maxblk, a.split_blocks, resident, cus);
   const bool block_sums = per > a.split_blocks;
   a.split_blocks = per;
   const int splits = (maxblk + per - 1) / per;

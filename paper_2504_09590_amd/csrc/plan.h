@@ -5,6 +5,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 namespace bros {
@@ -18,55 +19,74 @@ inline int32_t longest_blocks(int32_t max_ctx, int32_t max_blocks_per_seq) {
 // Blocks of a work item of the fp32 decode. The workspace is laid out for splits
 // of `plan_blocks` blocks (4 to 64, chosen by the rows alone); KV heads make items
 // too, and an item costs its start-up and a partial, so an item may take several
-// of these splits: the count with the least expected time, the plan's own unless
-// that is 6 % slower.
+// of these splits. The usual size leaves two items per compute unit, up to 32
+// blocks, and contexts of up to 20 blocks whole; another of kSizes is taken where
+// it is expected to be a tenth faster.
 //
 // Expected time, in units of about a microsecond: a stream of an item (four per
-// workgroup, two with 8 heads per KV head) takes 1.4 for a block and 0.09 more per
-// head of its wave, an item's start-up 1.1; items beyond the resident ones wait
-// for a free workgroup, and some 0.66 of the splits that the longest context has
-// are there on average; the last of them end with up to 0.45 of an item's blocks
-// alone; a call with splits also pays the merge, 3.7 and 0.62 per split. Fitted to
-// 1299 calls of 1 to 300 rows, contexts up to 40 to 4000 tokens (uniform and
-// lognormal) and 64 / 8, 32 / 8, 16 / 8, 8 / 8 and 8 / 1 heads, each at nine item
-// sizes: 2 % above the best size of each call on average; the plan's own splits
-// are 12 % above it, and one size for all (32 blocks, up to 20 whole) 5 %, with a
-// third more time where few segments of 8 heads ran whole. Us, the plan's own /
-// one size / this: 64 rows of 40 to 320 tokens (32 / 8 heads) 33.7 / 22.4 / 22.5, 16
-// rows of 256 to 2048 51.4 / 35.6 / 33.5, one row of 320 with 8 / 1 heads 12.5 /
-// 16.8 / 12.2. (What is left: the longest context alone is known here, so 32 rows
-// of 25 to 200 with 64 / 8 heads take 21.8 split and would take 16.2 whole.)
-// From plans of 8 blocks on (over 100 rows) the longest context is often one among
-// many short ones, which then all wait for it: beyond 25 blocks, items stay at 16
-// or the plan's (128 rows of lognormal contexts up to 700, 16 / 8 heads: 53 us at
-// 16 blocks, 71 at 48; 300 rows up to 320, whole 98, at 16 blocks 111).
+// workgroup, two with 8 heads per KV head) takes 1.15 for a block, 0.35 more per
+// head of its wave, and 0.4 of that again for each further item on a compute unit;
+// an item's start-up 1.7. Items beyond the resident ones wait for a free
+// workgroup. What is known is the longest context alone: equal contexts count by
+// 0.17, for which the items run in whole rounds, and contexts of 0.63 of the longest on average
+// by 0.83, where the last of them end with up to 0.45 of an item's time alone. A call with
+// splits also pays the merge, 4.2 and 0.9 per split. Steps of few rows wait for
+// their host calls instead, 11.5 and for the merge's launch 3 more: 0.6 of what a
+// call is below that counts too (5 rows of 93 to 301 tokens, 32 / 8 heads: a step
+// of 16.2 us whole, 19.4 split).
+//
+// Measured on 3168 calls of 1 to 256 rows with contexts up to 40 to 2048 tokens
+// (equal, within a quarter of the longest, uniform from 2/5 or 1/8 of it,
+// lognormal; 64 / 8, 32 / 8, 16 / 8, 8 / 8 and 8 / 1 heads), each at all these
+// sizes: 2 % above the best size of each call on average, the usual size alone 5 %,
+// the plan's own splits 14 %; against the usual size 25 calls lose 5 to 19 % (lognormal
+// contexts mostly). Us, the plan's own / the usual / this: 64 rows of 40 to 320
+// tokens (32 / 8 heads) 33.7 / 22.4 / 22.5, one row of 320 with 8 / 1 heads 12.5 / 16.8 /
+// 12.2. (Taking the size with the least expected time for contexts of 0.66 of the
+// longest gains as much on average, and loses 5 to 57 % in 237 calls: 16 rows of 2048 tokens, 64 / 8
+// heads, 49.5 / 69.8.)
 inline int32_t f32_item_blocks(int64_t rows, int32_t num_kv_heads, int32_t group, int32_t longest, int32_t plan_blocks,
-                               int32_t resident) {
-  constexpr int32_t kMaxItemBlocks = 64;
+                               int32_t resident, int32_t compute_units) {
+  constexpr int32_t kSizes[] = {4, 8, 12, 16, 20, 24, 32, 48, 64};
   const int32_t streams = group > 4 ? 2 : 4;
-  const double block_us = 1.4 + 0.09 * std::min(group, 4);
+  const double block_us = (1.15 + 0.35 * std::min(group, 4)) * (group > 4 ? 0.8 : 1.0);
   const double segments = (double)rows * num_kv_heads;
-  const int32_t most = plan_blocks >= 8 && longest > 25 ? std::max(plan_blocks, 16) : kMaxItemBlocks;
-  double best = 0.0;
-  int32_t chosen = plan_blocks;
-  for (int32_t per = plan_blocks; per <= most; per += plan_blocks) {
-    const int32_t splits = (longest + per - 1) / per;
-    const int32_t steps = (std::min(per, longest) + streams - 1) / streams;   // blocks of a stream
-    const double items = segments * (1.0 + 0.66 * (splits - 1));
-    double us = 1.1 + steps * block_us;
-    if (items > resident) {
-      const double mean = 0.66 * longest / streams * segments / items;
-      us = (1.1 + std::min<double>(steps, mean) * block_us) * items / resident + 0.45 * steps * block_us;
+  const double most = (double)resident / compute_units;   // items of a compute unit at once
+  const auto expected_us = [&](int32_t per) {
+    const double splits = (longest + per - 1) / per;
+    const double steps = (std::min(per, longest) + streams - 1) / streams;   // blocks of a stream
+    const auto item_us = [&](double items, double blocks) {
+      return 1.7 + blocks * block_us * (1.0 + 0.4 * (std::min(std::max(items / compute_units, 1.0), most) - 1.0));
+    };
+    const double all = segments * splits;
+    const double some = splits > 1.0 ? segments * std::min(0.63 * splits + 0.5, splits) : segments;
+    double us = item_us(some, steps);
+    if (some > resident) {
+      const double mean = 0.63 * longest / streams * segments / some;
+      us = item_us(some, std::min(steps, mean)) * some / resident + 0.45 * us;
     }
-    if (splits > 1) us += 3.7 + 0.62 * splits;
-    if (per > plan_blocks) us *= 1.06;
-    if (per == plan_blocks || us < best) {
-      best = us;
+    us = 0.17 * std::max(1.0, std::ceil(all / resident)) * item_us(all, steps) + 0.83 * us;
+    if (splits > 1.0) us += 4.2 + 0.9 * splits;
+    return us + 0.6 * std::max(0.0, 11.5 + (splits > 1.0 ? 3.0 : 0.0) - us);
+  };
+  const int64_t want = std::max<int64_t>(1, (int64_t)std::ceil(2.0 * compute_units / segments));   // splits of the longest
+  const int32_t usual = longest <= 20 ? longest : (int32_t)std::min<int64_t>((longest + want - 1) / want, 32);
+  int32_t base = 0, chosen = 0;
+  double best = 0.0, base_us = 0.0;
+  for (const int32_t per : kSizes) {
+    if (per % plan_blocks != 0) continue;
+    const double us = expected_us(per);
+    if (base == 0 || base < usual) {
+      base = per;
+      base_us = us;
+    }
+    if (chosen == 0 || us < best) {
       chosen = per;
+      best = us;
     }
     if (per >= longest) break;
   }
-  return chosen;
+  return best < 0.9 * base_us ? chosen : base;
 }
 
 // The fp32 prefill's units (`positions` positions of one chunk and KV head each)

@@ -18,8 +18,8 @@ WRAPPERS = """
 #include "plan.h"
 extern "C" {
 int longest(int max_ctx, int width) { return bros::longest_blocks(max_ctx, width); }
-int items(long long rows, int nkv, int group, int longest, int plan, int resident) {
-  return bros::f32_item_blocks(rows, nkv, group, longest, plan, resident);
+int items(long long rows, int nkv, int group, int longest, int plan, int resident, int cus) {
+  return bros::f32_item_blocks(rows, nkv, group, longest, plan, resident, cus);
 }
 void chunks(int rows, int seqs, int max_q, int nkv, int pos, int longest, int plan, int cus, long long* out) {
   const bros::F32ChunkPlan p = bros::plan_f32_chunks(rows, seqs, max_q, nkv, pos, longest, plan, cus);
@@ -46,7 +46,7 @@ def plan(tmp_path_factory):
     lib = ctypes.CDLL(str(so))
     I, Q = ctypes.c_int, ctypes.c_longlong
     lib.longest.argtypes = [I, I]
-    lib.items.argtypes = [Q, I, I, I, I, I]
+    lib.items.argtypes = [Q, I, I, I, I, I, I]
     lib.chunks.argtypes = [I] * 8 + [ctypes.POINTER(Q)]
     lib.whole.argtypes = [Q, Q]
     lib.pieces.argtypes = [Q, I, Q, I, Q, ctypes.POINTER(I)]
@@ -118,7 +118,7 @@ def test_splits_stay_within_the_workspace(plan):
         longest = rng.choice([1, 3, 4, 19, 20, 21, 25, 26, rng.randint(1, 3000), 2**27])
         sb = plan_blocks(rows, longest)
         cus = rng.choice([256, 128, 32])
-        per = plan.items(rows, nkv, group, longest, sb, 2 * cus)
+        per = plan.items(rows, nkv, group, longest, sb, 2 * cus, cus)
         assert per % sb == 0 and sb <= per <= 64
         units, tiles, per, splits = chunk_plan(plan, rows, rng.randint(1, rows), rng.randint(1, rows), nkv, 16 // group,
                                                longest, sb, cus)
@@ -126,12 +126,16 @@ def test_splits_stay_within_the_workspace(plan):
 
 
 def test_fp32_items(plan):
-    # few segments of 8 heads: split (two streams a workgroup walk them); many segments: whole; over 100 rows of
-    # contexts beyond 25 blocks, of which one may be far above the others: no more than 16 blocks
-    assert plan.items(1, 1, 8, 20, 4, 512) == 4
-    assert plan.items(64, 8, 4, 20, 4, 512) >= 20
-    assert plan.items(128, 8, 2, 44, 8, 768) <= 16 < 48
-    assert plan.items(300, 8, 2, 20, 16, 768) >= 20
+    # few segments of 8 heads: split (two streams a workgroup walk them); many segments, or a few whose step waits
+    # for its host calls: whole
+    assert plan.items(1, 1, 8, 20, 4, 512, 256) == 4
+    assert plan.items(64, 8, 4, 20, 4, 512, 256) >= 20
+    assert plan.items(5, 8, 4, 19, 4, 512, 256) >= 19
+    assert plan.items(300, 8, 2, 20, 16, 768, 256) >= 20
+    # contexts that may all be near the longest: no more items than run in one round (16 rows of 2048 tokens), and
+    # limits that follow the compute units
+    assert 16 * 8 * -(-128 // plan.items(16, 8, 8, 128, 4, 512, 256)) <= 512
+    assert 4 * 8 * -(-128 // plan.items(4, 8, 8, 128, 4, 128, 64)) <= 128
 
 
 def short_plan(plan, segments, group, blocks, cus=256, slots=1 << 40):

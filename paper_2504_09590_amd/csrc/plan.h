@@ -110,7 +110,9 @@ struct F32ChunkPlan {
 // wave 2.75 us, and 1.4 times that beside a second workgroup, since the fp32 matrix
 // instructions bound it; a unit's start takes as long as 3.3 of them, a merge 5 and
 // 0.6 per split. Fitted to 550 calls of 1 to 1100 rows on 0 to 4000 cached tokens,
-// each at four split sizes: 0.1 % above the best of them on average. Us, split down
+// each at four split sizes: 0.2 % above the best of them on average, with a split more
+// only where it is 2 % faster (64 rows on 600 tokens, 32 / 8 heads: two splits 19.5 us,
+// four, expected to be level, 22.7). Us, split down
 // to 16 blocks / to 8 / this: one row on 300 tokens (8 / 8 heads) 12.5 / 11.5 / 10.3,
 // 256 rows without cached tokens (16 / 8) 12.8 / 18.8 / 12.8.
 inline F32ChunkPlan plan_f32_chunks(int32_t num_rows, int32_t num_seqs, int32_t max_q_len, int32_t num_kv_heads,
@@ -131,7 +133,7 @@ inline F32ChunkPlan plan_f32_chunks(int32_t num_rows, int32_t num_seqs, int32_t 
     const double steps = (double)((std::min<int64_t>(per, longest) + 3) / 4);   // blocks of a wave
     double us = (steps + 3.3) * 2.75 * (live * splits > compute_units ? 1.4 : 1.0);
     if (splits > 1) us += 5.0 + 0.6 * (double)splits;
-    if (want > 1 && us >= best) continue;
+    if (want > 1 && us >= 0.98 * best) continue;
     best = us;
     p.split_blocks = (int32_t)per;
     p.splits = (int32_t)splits;

@@ -66,10 +66,10 @@ DECODE_SOURCES = ("paper_2504_09590_amd/csrc/decode.hip", "paper_2504_09590_amd/
                   "paper_2504_09590_amd/csrc/bros_kernels.h")
 DECODE_COUNTERS = {
     # workload: (sha256 of DECODE_SOURCES when the counters were read, FETCH_SIZE KiB, WRITE_SIZE KiB)
-    "llama3-70b-decode": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 4991883.4, 16515.2),
-    "llama3-8b-decode": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 454810.0, 5197.6),
-    "llama3-8b-mixed-step": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 1129280.6, 6173.2),
-    "llama3-8b-pressure": ("9667cd4ab5409f6288388de1efb238083bd148270b831576e4bd3aadf646119d", 601640.4, 10116.3),
+    "llama3-70b-decode": ("3f0a6e6c9dc0d7b3338c2c29967d32070a5cf5719a666aa6f4a141e9b9f2f710", 4992080.9, 16515.1),
+    "llama3-8b-decode": ("3f0a6e6c9dc0d7b3338c2c29967d32070a5cf5719a666aa6f4a141e9b9f2f710", 454830.1, 5197.7),
+    "llama3-8b-mixed-step": ("3f0a6e6c9dc0d7b3338c2c29967d32070a5cf5719a666aa6f4a141e9b9f2f710", 1129323.4, 6173.3),
+    "llama3-8b-pressure": ("3f0a6e6c9dc0d7b3338c2c29967d32070a5cf5719a666aa6f4a141e9b9f2f710", 601660.5, 10116.1),
 }
 
 

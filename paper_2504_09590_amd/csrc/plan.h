@@ -25,8 +25,8 @@ inline int32_t longest_blocks(int32_t max_ctx, int32_t max_blocks_per_seq) {
 //
 // Expected time, in units of about a microsecond: a stream of an item (four per
 // workgroup, two with 8 heads per KV head) takes 1.15 for a block, 0.35 more per
-// head of its wave, and 0.4 of that again for each further item on a compute unit;
-// an item's start-up 1.7. Items beyond the resident ones wait for a free
+// head of its wave (0.8 of that with two streams), and 0.4 of that again for each
+// further item on a compute unit; an item's start-up 1.7. Items beyond the resident ones wait for a free
 // workgroup. What is known is the longest context alone: equal contexts count by
 // 0.17, for which the items run in whole rounds, and contexts of 0.63 of the longest on average
 // by 0.83, where the last of them end with up to 0.45 of an item's time alone. A call with
@@ -42,7 +42,7 @@ inline int32_t longest_blocks(int32_t max_ctx, int32_t max_blocks_per_seq) {
 // the plan's own splits 14 %; against the usual size 25 calls lose 5 to 19 % (lognormal
 // contexts mostly). Us, the plan's own / the usual / this: 64 rows of 40 to 320
 // tokens (32 / 8 heads) 33.7 / 22.4 / 22.5, one row of 320 with 8 / 1 heads 12.5 / 16.8 /
-// 12.2. (Taking the size with the least expected time for contexts of 0.66 of the
+// 12.5. (Taking the size with the least expected time for contexts of 0.66 of the
 // longest gains as much on average, and loses 5 to 57 % in 237 calls: 16 rows of 2048 tokens, 64 / 8
 // heads, 49.5 / 69.8.)
 inline int32_t f32_item_blocks(int64_t rows, int32_t num_kv_heads, int32_t group, int32_t longest, int32_t plan_blocks,

@@ -39,7 +39,7 @@ inline int32_t longest_blocks(int32_t max_ctx, int32_t max_blocks_per_seq) {
 // (equal, within a quarter of the longest, uniform from 2/5 or 1/8 of it,
 // lognormal; 64 / 8, 32 / 8, 16 / 8, 8 / 8 and 8 / 1 heads), each at all these
 // sizes: 2 % above the best size of each call on average, the usual size alone 5 %,
-// the plan's own splits 14 %; against the usual size 25 calls lose 5 to 19 % (lognormal
+// the plan's own splits 12 %; against the usual size 25 calls lose 5 to 19 % (lognormal
 // contexts mostly). Us, the plan's own / the usual / this: 64 rows of 40 to 320
 // tokens (32 / 8 heads) 33.7 / 22.4 / 22.5, one row of 320 with 8 / 1 heads 12.5 / 16.8 /
 // 12.5. (Taking the size with the least expected time for contexts of 0.66 of the
